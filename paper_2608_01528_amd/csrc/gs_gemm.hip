@@ -1,4 +1,7 @@
-// Dense contractions of the Gram-Space operators on CDNA4 matrix cores.
+// Dense contractions of the Gram-Space operators on CDNA4 matrix cores: the
+// choice between the tile kernels (launch_gemm, below), the 128 x 128 tiles
+// for operands the others don't take (two element types, fewer than 16 bytes
+// of K, strides beyond their 32-bit offsets) and the argmax-only row sweep.
 //
 //   project      T = X Q^T          (A = X,  B = Q stored N x K)
 //   reconstruct  X = T Q            (A = T,  B = Q stored K x N)
@@ -1018,8 +1021,17 @@ hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi e
     const bool rows_ok = same && rows16(a.A, a.lda) && rows16(a.B, a.ldb) &&
                          (epi != EPI_BIND || rows16(a.A2, a.lda2));
     a.dma = rows_ok && ta == GS_BF16;   // the 128 x 128 pipelined loop is bf16 only
-    if (epi == EPI_STORE && rows_ok && gemm256_fits(ta, a, b_nn)) return launch_gemm256(ta, tout, b_nn, a, s);
-    if (epi == EPI_BIND && rows_ok && tout == GS_F32 && gemm256_fits(ta, a, b_nn)) {
+    const bool sm = epi == EPI_SOFTMAX;
+    const bool stores = epi == EPI_STORE || epi == EPI_BIND;
+    const bool scores = !b_nn && (sm || (epi == EPI_SIM && a.write_out));      // written to memory
+    // a few scores: one per work-group, its threads sharing the K range
+    if (scores && ta == tb && few_scores(a.M, a.N)) return launch_few_rows(ta, a, sm, s);
+    // 256 x 256 tiles where they fill the CUs, small tiles that share out the
+    // K range where they don't
+    const bool large = rows_ok && (epi != EPI_BIND || tout == GS_F32) && gemm256_fits(ta, a, b_nn);
+    if (same && (stores || scores) && split_fits(ta, b_nn, epi, a, large)) return launch_split(ta, tout, b_nn, epi, a, s);
+    if (epi == EPI_STORE && large) return launch_gemm256(ta, tout, b_nn, a, s);
+    if (epi == EPI_BIND && large) {
         // bound product on the large tiles: X = T Q, then X = X .* (T2 Q) in
         // the second product's epilogue (fp32 X holds the first factor exactly)
         GemmArgs first = a, second = a;
@@ -1046,18 +1058,17 @@ hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi e
         if (!bf_a && bf_b && bf_o) return dispatch_store<float, bf16_t, bf16_t>(b_nn, bind, a, veca, vecb, s);
         return hipErrorInvalidValue;
     }
-    const bool sm = epi == EPI_SOFTMAX;
-    // a few query rows: the K range is split over whole work-groups instead
-    // of walked by one tile
-    if (!b_nn && (sm || a.write_out) && a.M <= FEW_ROWS && ta == tb) return launch_few_rows(ta, a, sm, s);
-    // scores written, or whole rows in one tile (the row results come from
-    // the product's epilogue): the large tiles
-    if (rows_ok && !b_nn && (sm || a.write_out || a.N <= 256) && gemm256_fits(ta, a, false))
-        return launch_scores256(ta, a, sm, s);
-    if (rows_ok && !b_nn && sweep256_fits(ta, a)) return launch_sweep256(ta, sm, a, s);
+    if (scores && large) return launch_scores256(ta, a, sm, s);
+    // argmax alone: whole rows in one tile (the row results come from the
+    // product's epilogue), or a sweep over 256-row blocks, where a round of
+    // them fills the CUs
+    if (!b_nn && rows_ok && sweep256_fits(ta, a)) {
+        if (a.N <= 256 && gemm256_fits(ta, a, false)) return launch_scores256(ta, a, sm, s);
+        return launch_sweep256(ta, sm, a, s);
+    }
     // scores or weights written anyway: product with a scaled epilogue, then
     // the row pass; argmax alone: the row sweep (no score matrix in memory)
-    if ((sm || a.write_out) && !b_nn) {
+    if (scores) {
         if (!bf_a && !bf_b) return dispatch_scores<float, float>(sm, a, veca, vecb, s);
         if (bf_a && bf_b) return dispatch_scores<bf16_t, bf16_t>(sm, a, veca, vecb, s);
     }

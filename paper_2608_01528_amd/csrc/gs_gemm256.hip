@@ -1303,55 +1303,42 @@ __global__ void __launch_bounds__(256) rows_sim_attn_kernel(const float *W, int6
     for (int64_t c = l; c < M; c += 64) a[c] = __expf(beta * w[c] - mb) * iz;
 }
 
-// Scores of a few query rows (A, g.M rows) against every codebook row (B
-// stored N x K): one work-group per (query row, J codebook rows), the K range
-// split over its 256 threads, which also sum the squares for cosine norms
-// not given.  out[b, j] = scale * <a_b, b_j> (/ (||a_b|| ||b_j||) for cosine,
-// 0 if a norm is 0).
-template <typename T, int J>
+// A few scores (A: g.M query rows, B stored N x K: codebook rows): one
+// work-group per (query row, codebook row), the K range split over its 256
+// threads, which also sum the squares for cosine norms not given.  out[b, j] =
+// scale * <a_b, b_j> (/ (||a_b|| ||b_j||) for cosine, 0 if a norm is 0).
+template <typename T>
 __global__ void __launch_bounds__(256) few_rows_kernel(GemmArgs g) {
-    constexpr int NV = 2 * J + 1;   // J products, J codebook squares, the query square
-    const int64_t b = blockIdx.y;
-    const int64_t j0 = (int64_t)blockIdx.x * J;
-    const int nj = (g.N - j0 < J) ? (int)(g.N - j0) : J;
+    const int64_t b = blockIdx.y, j = blockIdx.x;
     const T *x = static_cast<const T *>(g.A) + b * g.lda;
-    const T *Bm = static_cast<const T *>(g.B) + j0 * g.ldb;
-    float v[NV];
-#pragma unroll
-    for (int i = 0; i < NV; ++i) v[i] = 0.f;
+    const T *y = static_cast<const T *>(g.B) + j * g.ldb;
+    float v[3] = {0.f, 0.f, 0.f};                   // product, codebook square, query square
     for (int64_t k = threadIdx.x; k < g.K; k += 256) {
-        const float xv = ld_f32<T>(x, k);
-        v[2 * J] += xv * xv;
-#pragma unroll
-        for (int j = 0; j < J; ++j)
-            if (j < nj) {
-                const float c = ld_f32<T>(Bm, (int64_t)j * g.ldb + k);
-                v[j] += xv * c;
-                v[J + j] += c * c;
-            }
+        const float xv = ld_f32<T>(x, k), c = ld_f32<T>(y, k);
+        v[0] += xv * c;
+        v[1] += c * c;
+        v[2] += xv * xv;
     }
 #pragma unroll
-    for (int i = 0; i < NV; ++i)
+    for (int i = 0; i < 3; ++i)
 #pragma unroll
         for (int o = 32; o >= 1; o >>= 1) v[i] += __shfl_xor(v[i], o);
-    __shared__ float part[4][NV];
+    __shared__ float part[4][3];
     const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
     if (l == 0) {
 #pragma unroll
-        for (int i = 0; i < NV; ++i) part[w][i] = v[i];
+        for (int i = 0; i < 3; ++i) part[w][i] = v[i];
     }
     __syncthreads();
-    if ((int)threadIdx.x < nj) {
-        const int j = threadIdx.x;
-        const float dot = part[0][j] + part[1][j] + part[2][j] + part[3][j];
+    if (threadIdx.x == 0) {
+        auto sum = [&](int i) { return part[0][i] + part[1][i] + part[2][i] + part[3][i]; };
         float f = g.scale;
         if (g.cosine) {
-            const float n2 = g.qnorm2 ? g.qnorm2[b] : part[0][2 * J] + part[1][2 * J] + part[2][2 * J] + part[3][2 * J];
-            const float c = g.cnorm ? g.cnorm[j0 + j]
-                                    : sqrtf(part[0][J + j] + part[1][J + j] + part[2][J + j] + part[3][J + j]);
+            const float n2 = g.qnorm2 ? g.qnorm2[b] : sum(2);
+            const float c = g.cnorm ? g.cnorm[j] : sqrtf(sum(1));
             f = (n2 > 0.f && c > 0.f) ? g.scale / (sqrtf(n2) * c) : 0.f;
         }
-        static_cast<float *>(g.C)[b * g.ldc + j0 + j] = dot * f;
+        static_cast<float *>(g.C)[b * g.ldc + j] = sum(0) * f;
     }
 }
 
@@ -1410,17 +1397,9 @@ hipError_t launch_few_rows(gs_dtype t, const GemmArgs &a, bool softmax, hipStrea
     if (a.M == 0 || a.N == 0) return hipSuccess;
     GemmArgs b = a;
     if (softmax) b.scale = a.scale * a.beta;      // the softmax acts on beta * score
-    // 8 codebook rows per work-group while that still gives a round of 256
-    // work-groups, else one (more work-groups, each reading its query again)
-    if (a.M * ((a.N + 7) / 8) >= 256) {
-        const dim3 grid((unsigned)((a.N + 7) / 8), (unsigned)a.M);
-        if (t == GS_BF16) hipLaunchKernelGGL((few_rows_kernel<bf16_t, 8>), grid, dim3(256), 0, s, b);
-        else hipLaunchKernelGGL((few_rows_kernel<float, 8>), grid, dim3(256), 0, s, b);
-    } else {
-        const dim3 grid((unsigned)a.N, (unsigned)a.M);
-        if (t == GS_BF16) hipLaunchKernelGGL((few_rows_kernel<bf16_t, 1>), grid, dim3(256), 0, s, b);
-        else hipLaunchKernelGGL((few_rows_kernel<float, 1>), grid, dim3(256), 0, s, b);
-    }
+    const dim3 grid((unsigned)a.N, (unsigned)a.M);
+    if (t == GS_BF16) hipLaunchKernelGGL((few_rows_kernel<bf16_t>), grid, dim3(256), 0, s, b);
+    else hipLaunchKernelGGL((few_rows_kernel<float>), grid, dim3(256), 0, s, b);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_rows_pass(softmax, static_cast<float *>(a.C), a.ldc, a.M, a.N, softmax ? nullptr : a.argmax, s);
@@ -1475,10 +1454,6 @@ hipError_t launch_sweep256(gs_dtype t, bool softmax, const GemmArgs &a, hipStrea
 }
 
 bool gemm256_fits(gs_dtype t, const GemmArgs &a, bool b_nn) {
-    // at least one full round of 256 x 256 tiles over the 256 CUs; smaller
-    // products keep the 128 x 128 tiles, which spread over more CUs
-    const int64_t total = ((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
-    if (total < 256) return false;
     // byte offsets within a tile's buffer resources stay below 2^31
     const int64_t es = elt_bytes(t), lim = ((int64_t)1 << 31) - 8192;
     if (es * (TM * a.lda + a.K + 8) >= lim) return false;

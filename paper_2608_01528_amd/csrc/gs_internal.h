@@ -128,10 +128,16 @@ hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi e
 
 // 256 x 256-tile product with a plain store (and optional row norms of A),
 // both operands of type t (bf16 or fp32) with 16-byte aligned rows.
-// gemm256_fits tells whether the product is large enough to fill the chip
-// with such tiles.
+// gemm256_fits tells whether their 32-bit offsets reach the operands.
 bool gemm256_fits(gs_dtype t, const GemmArgs &a, bool b_nn);
 hipError_t launch_gemm256(gs_dtype t, gs_dtype tout, bool b_nn, const GemmArgs &a, hipStream_t s);
+// Products with few output tiles (request-sized batches): small tiles, the K
+// range of a tile dealt to the waves of its work-group.  Both operands of type
+// t; EPI_SIM must write its scores (the row pass follows).  split_fits tells
+// whether the operands allow these tiles and, where the 256 x 256 tiles are
+// possible too (large_tiles), which of the two are the better ones.
+bool split_fits(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a, bool large_tiles);
+hipError_t launch_split(gs_dtype t, gs_dtype tout, bool b_nn, Epi epi, const GemmArgs &a, hipStream_t s);
 // Row sweep of similarity (softmax = false) or attention scores over 256 x
 // 256 blocks, same operand conditions (B stored N x K).
 bool sweep256_fits(gs_dtype t, const GemmArgs &a);
@@ -140,9 +146,12 @@ hipError_t launch_sweep256(gs_dtype t, bool softmax, const GemmArgs &a, hipStrea
 // product kernel with a scaled-score epilogue, then a row pass (argmax, or
 // softmax in place).  Same operand conditions as launch_gemm256 (B N x K).
 hipError_t launch_scores256(gs_dtype t, const GemmArgs &a, bool softmax, hipStream_t s);
-// Scores of a few query rows (a.M <= FEW_ROWS) written to a.C, then the row
-// pass (argmax, or softmax in place); any K, B stored N x K.
+// A few scores written to a.C (one work-group each, its threads sharing the K
+// range), then the row pass (argmax, or softmax in place); any K, B stored
+// N x K.  Up to 32 query rows and about 2048 scores: 1 x 1000 at K = 1000 takes
+// 3.8 us (10 us on 32 x 32 tiles), 8 x 1000 11.6 us (10 us).
 constexpr int64_t FEW_ROWS = 32;
+inline bool few_scores(int64_t rows, int64_t entries) { return rows <= FEW_ROWS && rows * ((entries + 7) / 8) < 256; }
 hipError_t launch_few_rows(gs_dtype t, const GemmArgs &a, bool softmax, hipStream_t s);
 // Row pass over a B x M fp32 score matrix (leading dimension ld): softmax in
 // place, or the row argmax (lowest index on ties) into argmax when non-null.
