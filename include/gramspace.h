@@ -102,8 +102,9 @@ typedef enum { GS_SIM_DOT = 0, GS_SIM_COSINE = 1 } gs_sim_mode;
  * above its diagonal (at r = M about half the work of P R, T R^T and A R);
  * for finite P, T and A the results are those of the same call without the
  * flag.  Entries of R above the diagonal may then go unread: if they are not
- * zero, the results are undefined.  Cosine scores whose ||x_b|| comes from T
- * (qnorm2 == NULL) keep the full range.
+ * zero, the results are undefined.  Attention weights (gs_attention) whose
+ * ||x_b|| comes from T (qnorm2 == NULL) keep the full range, as do cosine
+ * scores then if no argmax is asked for.
  */
 #define GS_ECHELON 0x100
 

@@ -517,6 +517,7 @@ gs_status gs_similarity(const void *T, gs_dtype tt, int64_t B, int64_t r, int64_
     a.A = T; a.lda = ldt; a.B = R; a.ldb = ldr; a.C = S; a.ldc = lds; a.M = B; a.N = M; a.K = r;
     a.qnorm2 = qnorm2; a.cnorm = cnorm; a.cosine = mode == GS_SIM_COSINE; a.scale = scale;
     a.argmax = argmax; a.write_out = S != nullptr; a.echelon = ech;
+    a.norm_scratch = reinterpret_cast<float *>(argmax);      // the row pass writes the indices last
     return launched(launch_gemm(tt, rt, GS_F32, false, EPI_SIM, a, (hipStream_t)stream), "gs_similarity");
 }
 
@@ -592,6 +593,7 @@ gs_status gs_similarity_attention(const void *T, gs_dtype tt, int64_t B, int64_t
         a.A = T; a.lda = ldt; a.B = R; a.ldb = ldr; a.C = W; a.ldc = ldw; a.M = B; a.N = M; a.K = r;
         a.qnorm2 = qnorm2; a.cnorm = cnorm; a.cosine = mode == GS_SIM_COSINE; a.scale = scale;
         a.write_out = true; a.echelon = ech;
+        a.norm_scratch = reinterpret_cast<float *>(argmax);  // the row pass writes the indices last
         GS_CHECK(launched(launch_gemm(tt, rt, GS_F32, false, EPI_SIM, a, s), fn));
     }
     // one pass over the scores: the row argmax and the weights

@@ -112,6 +112,8 @@ struct GemmArgs {
     int64_t M, N, K;
     float *rownorm2;                   // EPI_STORE: sum_k A[m,k]^2, nullable
     const float *qnorm2;               // SIM / SOFTMAX, nullable
+    float *norm_scratch;               // SIM: M floats that may be overwritten (an output written
+                                       // after the scores), nullable
     const float *cnorm;                // SIM / SOFTMAX, nullable
     int cosine;
     float scale;

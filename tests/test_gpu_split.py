@@ -142,3 +142,32 @@ def test_split_infinities_stay_in_their_row():
     want[7, :] = True
     want[:, 3] = True
     assert torch.equal(bad, want)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("r", [500, 505])
+def test_scores_with_norms_summed_in_their_own_pass(dtype, r):
+    """Cosine scores of a full batch over several column tiles without given
+    norms: ||t|| from a pass over T, scores and winners as with the 64-bit
+    norms, flagged and unflagged alike (also for gs_similarity_attention)."""
+    gs = _gs()
+    B, M = 33000, 520
+    T, t = operand(B, r, dtype, 21, "aligned")
+    R, _ = operand(M, r, dtype, 22, "aligned")
+    R.copy_(torch.tril(R))
+    T[5, :] = 0
+    t[5, :] = 0
+    r64 = R.cpu().double().numpy()
+    S0, i0 = gs.gs_similarity(T, R)
+    S1, i1 = gs.gs_similarity(T, R, echelon=True)
+    S2, i2, _ = gs.gs_similarity_attention(T, R, echelon=True)
+    assert torch.equal(S0, S1) and torch.equal(i0, i1) and torch.equal(S0, S2) and torch.equal(i0, i2)
+    rows = np.concatenate([np.arange(300), np.arange(B - 300, B)])
+    nx, nr = np.linalg.norm(t[rows], axis=1), np.linalg.norm(r64, axis=1)
+    f = 1.0 / np.maximum(nx[:, None] * nr[None, :], 1e-30)
+    exact = f * (t[rows] @ r64.T)
+    bound = f * gamma(r + 8) * (np.abs(t[rows]) @ np.abs(r64.T)) + (gamma(r + 8) + 1e-6) * np.abs(exact) + 1e-30
+    g = S1[torch.from_numpy(rows).cuda()].cpu().double().numpy()
+    assert np.all(np.abs(g - exact) <= bound)
+    assert torch.equal(i1.long(), S1.argmax(1)) or torch.all(S1.gather(1, i1.long()[:, None])[:, 0] == S1.amax(1))
+    assert int(i1[5]) == 0 and torch.all(S1[5] == 0)
