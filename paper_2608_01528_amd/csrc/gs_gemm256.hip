@@ -7,7 +7,9 @@
 // Work-group tile 256 x 256, 512 threads = 8 waves in a 2 x 4 arrangement;
 // each wave owns a 128 x 64 sub-tile as 4 x 2 blocks of the 32 x 32 MFMA
 // (32x32x16 bf16 or 32x32x2 fp32), 128 accumulators, two waves per SIMD so
-// that one wave's waits overlap the other's matrix work.  A K-step of 64
+// that one wave's waits overlap the other's matrix work (fp32 products with a
+// stored result split their operands and run on the bf16 form: see
+// mma_256_planes).  A K-step of 64
 // bf16 or 32 fp32 makes every row slice a whole 128-byte line, so L2 serves
 // the operands in full-line requests.
 //
@@ -450,6 +452,218 @@ __device__ __forceinline__ void mma_256(const GemmArgs &g, const TileLoads<T, BN
     }
 }
 
+// ---------------------------------------------------------- fp32 as three bf16
+//
+// An fp32 product on the bf16 matrix cores: x = h + m + l with h = bf16(x),
+// m = bf16(x - h), l = bf16(x - h - m), exact for all 24 bits, and
+//   x y = h h' + (h m' + m h') + (h l' + m m' + l h')
+// up to 2^-24 |x y|: six MFMAs of 32x32x16 bf16 (32 cycles each) in place of
+// eight of 32x32x2 fp32 (64 cycles).  A running sum is rounded once per K-step of
+// 16 instead of eight times, so the error falls with the time.
+//
+// Rows are split once per work-group on their way into LDS: a thread loads 8
+// consecutive k of one row (or column, K x N) of each operand into registers a
+// K-step ahead, splits them and writes one 16-byte chunk per plane.  Two stages
+// of 48 KiB (K-step 16, six planes), one barrier per K-step.  A plane keeps
+// the 32 rows x 16 k of an MFMA operand as the 1 KiB that one ds_read_b128 of a
+// wave fetches, the second k-half's rows exchanged in eights, so that neither
+// those reads nor the staging writes (neighbouring lanes: the two halves of a
+// row) collide on banks.
+//
+// Both operands are scaled by 2^16 on the way (and the sums by 2^-32), so that
+// the low parts of any normal fp32 value are normal numbers too.  What has no
+// such parts (infinities, NaN, values of 2^111 and up, sums past the range)
+// leaves a sum that is not finite: the caller then runs the tile once more
+// with fp32 MFMAs.
+//
+// What bounds it is power: the matrix cores are busy 59 % of the time at 1.83
+// GHz (bf16 operands: 73 % at 1.42).  65536 x 256 x 8192 (project): 1.94 ms with
+// fp32 MFMAs, 1.48 now; 16384 x 1000 x 4096: 970 -> 747 us; the error against 64
+// bits of these results 1.4e-6 -> 6.4e-7 and 1.5e-6 -> 3.7e-7.  With the
+// six products added straight to the running sums it is 7 % faster, but
+// positive sums (a binary codebook's) then round further off than in fp32
+// (1.6e-6).
+constexpr int PK = 16;                              // K-step
+constexpr int PLANE = TM * PK;                      // 16-bit units of a plane (8 KiB)
+constexpr int PSTAGE = 6 * PLANE;                   // A's planes h, m, l, then B's
+constexpr float PSCALE = 0x1p16f, PUNSCALE = 0x1p-32f;
+static_assert(2 * PSTAGE <= NSTAGE * 2 * OPT, "the planes fit the stages of the fp32 form");
+
+__device__ __forceinline__ float as_f32(uint32_t u) { return __uint_as_float(u); }
+
+// Planes of 8 values, scaled.
+__device__ __forceinline__ void split8(const float x[8], u32x4 p[3]) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        float a = x[2 * i] * PSCALE, b = x[2 * i + 1] * PSCALE;
+        p[0][i] = pack_bf16(a, b);
+        a -= as_f32(p[0][i] << 16);
+        b -= as_f32(p[0][i] & 0xffff0000u);
+        p[1][i] = pack_bf16(a, b);
+        a -= as_f32(p[1][i] << 16);
+        b -= as_f32(p[1][i] & 0xffff0000u);
+        p[2][i] = pack_bf16(a, b);
+    }
+}
+
+// mma_256 for fp32 operands by the split above (eight waves; acc, sq and sb as
+// there).  Returns false, in every thread, when the tile has to be redone.
+template <bool BNN, bool SQA, bool SQB, bool SWP>
+__device__ __forceinline__ bool mma_256_planes(const GemmArgs &g, int64_t m0, int64_t n0, uint16_t *lds,
+                                               f16v acc[4][2], bool sqa, float sq[4], bool sqb, float sb[2],
+                                               int64_t k_lo, int64_t k_hi, int tid) {
+    const int l = tid & 63, w = tid >> 6;
+    const int wm = Waves<8>::wm(w), wn = Waves<8>::wn(w);
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) acc[i][j] = f16v{};
+    // this thread's share of the staging: 8 k (half ha or hb of the K-step) of
+    // one row of A, and of one row (N x K) or column (K x N) of B; rows and
+    // columns past the matrix are its last one
+    const int ra = tid >> 1, ha = tid & 1;
+    const int rb = BNN ? (tid & 255) : ra, hb = BNN ? (tid >> 8) : ha;
+    const int64_t arow = (m0 + ra < g.M) ? m0 + ra : g.M - 1, brow = (n0 + rb < g.N) ? n0 + rb : g.N - 1;
+    const float *pa = static_cast<const float *>(g.A) + arow * g.lda;
+    const float *pb = static_cast<const float *>(g.B) + (BNN ? brow : brow * g.ldb);
+    auto slot = [&](int r, int h) { return (r >> 5) * 512 + h * 256 + (((r & 31) ^ (8 * h)) << 3); };
+    const int wa = slot(ra, ha), wb = 3 * PLANE + slot(rb, hb);
+    const int rd = slot(l & 31, l >> 5);
+    const int K = (int)g.K, klast = (K - 1) / 4 * 4, kend = (int)k_hi;
+    const int ldb = (int)g.ldb;
+    float va[8], vb[8];
+    auto load = [&](int k0) {
+        auto row8 = [&](const float *p, int k, float v[8]) {
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const int kc = (k + 4 * u < klast) ? k + 4 * u : klast;
+                const f4v x = *reinterpret_cast<const f4v *>(p + kc);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[4 * u + e] = x[e];
+            }
+        };
+        row8(pa, k0 + 8 * ha, va);
+        if constexpr (BNN) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                const int k = k0 + 8 * hb + e;
+                vb[e] = pb[(int64_t)(k < K - 1 ? k : K - 1) * ldb];
+            }
+        } else {
+            row8(pb, k0 + 8 * hb, vb);
+        }
+    };
+    float na = 0.f, nb = 0.f;                        // squares of the staged values
+    // (`tail`: the K-step may reach past the range's end, where zeros go)
+    auto put = [&](float v[8], int k, bool tail, bool sum, float &n, uint16_t *dst) {
+        if (tail) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = (k + e < kend) ? v[e] : 0.f;
+        }
+        if (sum) {
+#pragma unroll
+            for (int e = 0; e < 8; ++e) n += v[e] * v[e];
+        }
+        u32x4 p[3];
+        split8(v, p);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4 *>(dst + q * PLANE) = p[q];
+    };
+    auto put_a = [&](int k0, bool tail, uint16_t *st) { put(va, k0 + 8 * ha, tail, SQA && sqa, na, st + wa); };
+    auto put_b = [&](int k0, bool tail, uint16_t *st) { put(vb, k0 + 8 * hb, tail, SQB && sqb, nb, st + wb); };
+    auto frag = [&](const uint16_t *plane, int r0) {
+        return *reinterpret_cast<const bf8v *>(plane + (r0 >> 5) * 512 + rd);
+    };
+    int k0 = (int)k_lo;
+    load(k0);
+    put_a(k0, true, lds);
+    put_b(k0, true, lds);
+    load(k0 + PK);
+    lds_barrier();
+    // One block's share of a K-step: the six products from zero, smallest
+    // first; the block's running sum takes their total in one rounded addition
+    // (rather than six of the matrix cores').
+    constexpr int QA[6] = {0, 2, 1, 0, 1, 0}, QB[6] = {2, 0, 1, 1, 0, 0};
+    auto products = [&](const bf8v fa[3], const bf8v fb[3]) {
+        f16v c = f16v{};
+#pragma unroll
+        for (int q = 0; q < 6; ++q)
+            c = SWP ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(fb[QB[q]], fa[QA[q]], c, 0, 0, 0)
+                    : __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[QA[q]], fb[QB[q]], c, 0, 0, 0);
+        return c;
+    };
+    uint16_t *cur = lds, *nxt = lds + PSTAGE;
+    auto step = [&](bool tail) {
+        bf8v fb[2][3], fa[2][3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+            fa[0][q] = frag(cur + q * PLANE, wm);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) fb[j][q] = frag(cur + (3 + q) * PLANE, wn + 32 * j);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int j = 0; j < 2; ++j) {
+                const f16v part = products(fa[i & 1], fb[j]);
+                __builtin_amdgcn_sched_barrier(0);
+                // beside the matrix work: the next rows' fragments, and the
+                // next K-step's values from registers into the other stage
+                if (j == 0 && i < 3) {
+#pragma unroll
+                    for (int q = 0; q < 3; ++q) fa[(i + 1) & 1][q] = frag(cur + q * PLANE, wm + 32 * (i + 1));
+                }
+                if (j == 1 && i == 0) put_a(k0 + PK, tail, nxt);
+                if (j == 1 && i == 1) put_b(k0 + PK, tail, nxt);
+                if (j == 1 && i == 2) load(k0 + 2 * PK);
+                __builtin_amdgcn_sched_barrier(0);
+                acc[i][j] += part;
+                asm volatile("" : "+v"(acc[i][j]));      // (added here, not later)
+            }
+        lds_barrier();
+        uint16_t *t = cur;
+        cur = nxt;
+        nxt = t;
+        k0 += PK;
+    };
+    while (k0 + 2 * PK <= kend) step(false);
+    while (k0 < kend) step(true);
+    if ((SQA && sqa) || (SQB && sqb)) {
+        // row norms to the lanes that mma_256 leaves them in (both halves' sum in the lower lane)
+        float *norms = reinterpret_cast<float *>(lds);
+        na += __shfl_xor(na, 1);
+        nb += __shfl_xor(nb, 1);
+        if (ha == 0) {
+            norms[ra] = na;
+            norms[TM + ra] = nb;
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < 4; ++i) sq[i] = l < 32 ? norms[wm + 32 * i + l] : 0.f;
+        if (SQB) {
+#pragma unroll
+            for (int j = 0; j < 2; ++j) sb[j] = l < 32 ? norms[TM + wn + 32 * j + l] : 0.f;
+        }
+    }
+    float z = 0.f;                                   // NaN when a sum is not finite
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+#pragma unroll
+            for (int e = 0; e < 16; ++e) z += 0.f * acc[i][j][e];
+            acc[i][j] *= PUNSCALE;
+        }
+    const bool bad = __any(z != z);
+    uint32_t *votes = reinterpret_cast<uint32_t *>(lds + 2 * PSTAGE);
+    if (l == 0) votes[w] = bad;
+    lds_barrier();
+    uint32_t redo = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) redo |= votes[u];
+    return __builtin_amdgcn_readfirstlane(redo) == 0;
+}
+
 // Tile order shared by the 256 x 256 kernels.  Work-group ids are dealt to
 // the 8 XCDs round robin, so XCD x runs logical tiles [x per, (x + 1) per);
 // in logical order, groups of GROUP_M m-tiles take each n-tile in turn, so
@@ -501,6 +715,8 @@ gemm256_store_kernel(GemmArgs g) {
     typedef Waves<GEMM_NW> W;
     constexpr int NJ = W::NJ, WTN = W::WTN, TK = Op<T>::TK;
     constexpr bool SWP = sizeof(TO) == 2;                    // transposed accumulator blocks
+    constexpr bool PLANES = sizeof(T) == 4;                  // fp32 operands as three bf16
+    static_assert(!PLANES || PSTAGE <= 2 * OPT, "the epilogue's staging clear of the first planes");
     constexpr int PR = sizeof(TO) == 2 ? 32 : 16;            // rows per staging pass
     constexpr int RP = PR / 2;                               // accumulator registers per pass (fp32)
     constexpr int EPC = 16 / (int)sizeof(TO);                // elements per 16-byte chunk
@@ -528,8 +744,10 @@ gemm256_store_kernel(GemmArgs g) {
     TileLoads<T, BNN, GEMM_NW> tl;
     tl.init(g, m0, n0);
     int slot0 = 0, pending = 0;
-    tl.issue(g, k_lo / TK, 0, stage_slot(lds, slot0), threadIdx.x);
-    tl.issue(g, k_lo / TK, 1, stage_slot(lds, slot0), threadIdx.x);
+    if (!PLANES) {
+        tl.issue(g, k_lo / TK, 0, stage_slot(lds, slot0), threadIdx.x);
+        tl.issue(g, k_lo / TK, 1, stage_slot(lds, slot0), threadIdx.x);
+    }
     for (;;) {
         // the thread id passes through an empty asm per tile, so the
         // lane-dependent addresses are recomputed here rather than kept live
@@ -543,8 +761,19 @@ gemm256_store_kernel(GemmArgs g) {
         // the rownorm2 side output of the tiles with n0 == 0
         const bool sqa = a_norms && n0 == 0 && wn == 0;
         float sq[4] = {0.f, 0.f, 0.f, 0.f}, sb[NJ];
-        mma_256<T, BNN, true, false, GEMM_NW, SWP>(g, tl, lds, slot0, true, pending, acc, sqa, sq, false, sb,
-                                                   k_lo, k_hi, tid);
+        if constexpr (PLANES) {
+            if (!mma_256_planes<BNN, true, false, SWP>(g, m0, n0, lds, acc, a_norms && n0 == 0, sq, false, sb, k_lo,
+                                                       k_hi, tid)) {
+#pragma unroll
+                for (int i = 0; i < 4; ++i) sq[i] = 0.f;
+                mma_256<T, BNN, true, false, GEMM_NW, SWP>(g, tl, lds, 0, false, 0, acc, sqa, sq, false, sb, k_lo,
+                                                           k_hi, tid);
+                __syncthreads();          // (the next tile's planes go where these stages are)
+            }
+        } else {
+            mma_256<T, BNN, true, false, GEMM_NW, SWP>(g, tl, lds, slot0, true, pending, acc, sqa, sq, false, sb,
+                                                       k_lo, k_hi, tid);
+        }
         if (sqa) {
             // lanes l and l + 32 hold the two k-halves of row wm + 32 i + l % 32
 #pragma unroll
@@ -554,8 +783,9 @@ gemm256_store_kernel(GemmArgs g) {
                 if (l < 32 && row < g.M) g.rownorm2[row] = t;
             }
         }
-        // the next tile's first stage, into the slot the last K-step did not read
-        const int next_slot = (int)((slot0 + (k_hi + TK - 1) / TK - k_lo / TK) & 1);
+        // the next tile's first stage, into the slot the last K-step did not
+        // read (planes: the epilogue is staged past the first of them)
+        const int next_slot = PLANES ? 0 : (int)((slot0 + (k_hi + TK - 1) / TK - k_lo / TK) & 1);
         const int64_t nlt = lt + nq;
         const bool has_next = nlt < lt_end;
         int64_t m1 = 0, n1 = 0, k_lo1 = 0, k_hi1 = 0;
@@ -564,8 +794,10 @@ gemm256_store_kernel(GemmArgs g) {
             tile_of(nlt, nM, nN, m1, n1);
             k_range<T, BNN>(g, n1, a_norms, k_lo1, k_hi1);
             tl1.init(g, m1, n1);
-            tl1.issue(g, k_lo1 / TK, 0, stage_slot(lds, next_slot), tid);
-            tl1.issue(g, k_lo1 / TK, 1, stage_slot(lds, next_slot), tid);
+            if (!PLANES) {
+                tl1.issue(g, k_lo1 / TK, 0, stage_slot(lds, next_slot), tid);
+                tl1.issue(g, k_lo1 / TK, 1, stage_slot(lds, next_slot), tid);
+            }
         }
 
         // whole tile inside the output, rows 16-byte aligned: staged 16-byte stores
@@ -704,7 +936,19 @@ scores256_kernel(GemmArgs g) {
     k_range<T, BNN>(g, n0, g.cosine && g.qnorm2 == nullptr, k_lo, k_hi);
     TileLoads<T, BNN, GEMM_NW> tl;
     tl.init(g, m0, n0);
-    mma_256<T, BNN, true, SCALED, GEMM_NW>(g, tl, lds, 0, false, 0, acc, sqa, sq, sqb, sb, k_lo, k_hi, threadIdx.x);
+    bool done = false;
+    if constexpr (sizeof(T) == 4) {
+        done = mma_256_planes<BNN, true, SCALED, false>(g, m0, n0, lds, acc, g.cosine && g.qnorm2 == nullptr, sq,
+                                                        g.cosine && g.cnorm == nullptr, sb, k_lo, k_hi, threadIdx.x);
+        if (!done) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) sq[i] = 0.f;
+#pragma unroll
+            for (int j = 0; j < NJ; ++j) sb[j] = 0.f;
+        }
+    }
+    if (!done)
+        mma_256<T, BNN, true, SCALED, GEMM_NW>(g, tl, lds, 0, false, 0, acc, sqa, sq, sqb, sb, k_lo, k_hi, threadIdx.x);
 
     float *rq = lds_f + LDS_BYTES / sizeof(float);   // SCALED: scale / ||x|| per row of the tile
     float *cn = rq + TM;                             // SCALED: 1 / ||c|| per column of the tile
