@@ -124,6 +124,34 @@ gs_status launched(hipError_t e, const char *what) {
 
 bool is_batch_type(gs_dtype t) { return t == GS_F32 || t == GS_BF16; }
 
+// Small codebooks (r <= M <= 64): the streaming kernels (one thread per row,
+// whole rows in LDS) or the matrix-core product on small tiles (gs_split.hip).
+// A thread's serial M x r loop is what the streaming kernels spend their time
+// on from 16 entries up, while the tiles share a row out over lanes; the
+// streaming kernels fold the row results in, the product needs a pass over the
+// scores for them, whose traffic counts from some 20000 rows on.  Times in us,
+// streaming and product, fp32 (bf16 alike):
+//   prob2vec  M = 12, 1024 rows 3.8, 3.9;  M = 16 5.3, 3.9;  M = 40 12.3, 3.7;
+//             65536 rows M = 16 6.0, 5.5;  M = 64 33.8, 12.2;
+//             200000 rows bf16 M = 24 10.3, 19.3;  M = 40 36.9, 19.6
+//   scores + weights (a pass follows either)  3001 rows M = 10 8.2, 8.8;
+//             M = 16 10.4, 9.1;  M = 40 17.4, 9.0;  65536 rows M = 16 37.2, 34.9
+//   scores + argmax  3001 rows M = 24 7.7, 8.0;  M = 32 14.9, 7.7;
+//             16384 rows M = 40 14.0, 12.1;  65536 rows 14.3, 28.8
+//   weights   1024 rows M = 40 17.3, 7.8;  16384 rows 18.2, 13.5
+// (fewer than 8 coordinates do not fill a 16-byte piece of the tiles' loads)
+constexpr int64_t TILE_MIN_M = 16, TILE_MIN_R = 8, TILE_MAX_B = 65536, TILE_PASS_M = 25, TILE_PASS_B = 16384;
+bool tiled_product(int64_t B, int64_t M, int64_t r) {
+    return r >= TILE_MIN_R && M >= TILE_MIN_M && (M > 32 || B <= TILE_MAX_B);
+}
+bool small_prob2vec(int64_t B, int64_t M, int64_t r) { return M <= SMALL_MAX && r <= M && !tiled_product(B, M, r); }
+// scores whose row results come from a pass of their own in either case
+bool small_scores_for_pass(int64_t B, int64_t M, int64_t r) {
+    return M <= SMALL_MAX && r <= M && B > FEW_ROWS && !tiled_product(B, M, r);
+}
+// scores or weights whose row results the streaming kernel would fold in
+bool tiled_scores(int64_t B, int64_t M, int64_t r) { return r >= TILE_MIN_R && M >= TILE_PASS_M && B <= TILE_PASS_B; }
+
 }  // namespace
 
 extern "C" {
@@ -433,10 +461,9 @@ gs_status gs_prob2vec(const void *P, gs_dtype pt, int64_t B, int64_t M, int64_t 
                             {span(T, B, r, ldt, esize(tt), "T")}));
     if (B == 0) return ok();
     GS_CHECK(check_device());
-    // small-codebook kernel for r <= M <= 64 (the codebook block is padded
-    // to M's size); more coordinates than entries (a padded basis) and larger
-    // codebooks take the matrix-core product
-    if (M <= SMALL_MAX && r <= M) {
+    // small-codebook kernel (the codebook block is padded to M's size) or the
+    // matrix-core product
+    if (small_prob2vec(B, M, r)) {
         SmallArgs a{};
         a.In = P; a.ldin = ldp; a.R = R; a.ldr = ldr; a.B = B; a.M = M; a.r = r; a.Out = T; a.ldout = ldt;
         return launched(launch_small_prob2vec(pt, tt, a, (hipStream_t)stream), "gs_prob2vec");
@@ -505,9 +532,9 @@ gs_status gs_similarity(const void *T, gs_dtype tt, int64_t B, int64_t r, int64_
                             {span(S, B, M, lds, 4, "S"), span(argmax, 1, B, B, 4, "argmax")}));
     if (B == 0) return ok();
     GS_CHECK(check_device());
-    // small-codebook kernels (one thread per row of r <= M <= 64), unless a
-    // few rows write their scores: those split the K reduction over work-groups
-    if (M <= SMALL_MAX && r <= M && !(B <= FEW_ROWS && S)) {
+    // small-codebook kernels, unless a few rows write their scores: those
+    // split the K reduction over work-groups
+    if (M <= SMALL_MAX && r <= M && !(S && (B <= FEW_ROWS || tiled_scores(B, M, r)))) {
         SmallArgs a{};
         a.In = T; a.ldin = ldt; a.R = R; a.ldr = ldr; a.B = B; a.M = M; a.r = r; a.Out = S; a.ldout = lds;
         a.qnorm2 = qnorm2; a.cnorm = cnorm; a.cosine = mode == GS_SIM_COSINE; a.scale = scale; a.argmax = argmax;
@@ -538,7 +565,7 @@ gs_status gs_attention(const void *T, gs_dtype tt, int64_t B, int64_t r, int64_t
     if (B == 0) return ok();
     GS_CHECK(check_device());
     hipStream_t s = (hipStream_t)stream;
-    if (M <= SMALL_MAX && r <= M && B > FEW_ROWS) {   // small-codebook kernels, as in gs_similarity
+    if (M <= SMALL_MAX && r <= M && B > FEW_ROWS && (O || !tiled_scores(B, M, r))) {   // as in gs_similarity
         SmallArgs a{};
         a.In = T; a.ldin = ldt; a.R = R; a.ldr = ldr; a.B = B; a.M = M; a.r = r; a.Out = A; a.ldout = lda;
         a.O = O; a.ldo = ldo; a.qnorm2 = qnorm2; a.cnorm = cnorm; a.cosine = mode == GS_SIM_COSINE;
@@ -583,7 +610,7 @@ gs_status gs_similarity_attention(const void *T, gs_dtype tt, int64_t B, int64_t
     // the scores once, into S (or into A, replaced there by the weights)
     float *W = S ? S : A;
     const int64_t ldw = S ? lds : lda;
-    if (M <= SMALL_MAX && r <= M && B > FEW_ROWS) {
+    if (small_scores_for_pass(B, M, r)) {
         SmallArgs a{};
         a.In = T; a.ldin = ldt; a.R = R; a.ldr = ldr; a.B = B; a.M = M; a.r = r; a.Out = W; a.ldout = ldw;
         a.qnorm2 = qnorm2; a.cnorm = cnorm; a.cosine = mode == GS_SIM_COSINE; a.scale = scale;
