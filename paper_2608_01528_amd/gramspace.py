@@ -125,20 +125,27 @@ def _check(status: int):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _mat(t: torch.Tensor, name: str):
+    # (each tensor attribute is asked for once: these checks are most of what a
+    # small call costs on the host)
+    shape, stride = t.shape, t.stride()
+    two_d = len(shape) == 2
+    empty = two_d and (shape[0] == 0 or shape[1] == 0)
     # an empty matrix has no layout to check (its strides are arbitrary)
-    if t.dim() != 2 or (t.numel() > 0 and t.size(1) > 1 and t.stride(1) != 1):
+    if not two_d or (not empty and shape[1] > 1 and stride[1] != 1):
         raise ValueError("%s must be a 2-D row-major tensor (unit column stride)" % name)
     if not t.is_cuda:
         raise ValueError("%s must be on the GPU" % name)
-    if t.dtype not in _DT:
+    dt = _DT.get(t.dtype)
+    if dt is None:
         raise ValueError("%s: unsupported dtype %s" % (name, t.dtype))
-    if t.numel() == 0:
-        return _DT[t.dtype], max(t.size(1), 1)
-    return _DT[t.dtype], max(t.stride(0), t.size(1))
+    cols = shape[1]
+    if empty:
+        return dt, max(cols, 1)
+    return dt, max(stride[0], cols)
 
 
 def _shape(t, name: str, rows=None, cols=None):
@@ -146,7 +153,8 @@ def _shape(t, name: str, rows=None, cols=None):
     shape disagrees with them would be read or written past its end."""
     if t is None:
         return
-    if t.dim() != 2 or (rows is not None and t.shape[0] != rows) or (cols is not None and t.shape[1] != cols):
+    shape = t.shape
+    if len(shape) != 2 or (rows is not None and shape[0] != rows) or (cols is not None and shape[1] != cols):
         raise ValueError("%s must be %s x %s, got %s" % (name, "?" if rows is None else rows,
                                                          "?" if cols is None else cols, tuple(t.shape)))
 
@@ -166,7 +174,8 @@ def alloc_rows(rows: int, cols: int, dtype, device) -> torch.Tensor:
 
 
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle of torch.cuda.current_stream(), without the Stream object
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _mode(mode):
