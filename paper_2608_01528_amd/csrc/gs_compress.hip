@@ -14,8 +14,12 @@
 //     runs while that panel is factored (on a second stream when one is
 //     given, otherwise before it on the same stream; the results are the
 //     same bit for bit);
-//  2. the rows of the panel are orthogonalised among themselves in the small
-//     space of the panel's triangular factor: W^T = Q_t R_t by a tree of
+//  2. the rows of the panel are orthogonalised among themselves in a small
+//     space.  Where every row is clearly dependent (its norm is below the
+//     threshold already) or clearly independent (its pivot is not small against
+//     ||c_i||), that is the Cholesky factor of the panel's Gram matrix: two
+//     short kernels.  A panel with any other row takes the triangular factor
+//     of the panel itself (no squares): W^T = Q_t R_t by a tree of
 //     Householder factorisations (TSQR), so the columns a_i of R_t have the
 //     inner products of the rows w_i.  Modified Gram-Schmidt runs on those
 //     32-entry columns in index order, with a second projection for a column
@@ -115,7 +119,8 @@ struct Panel {
     int64_t i0;                 // first codebook row of the panel
     int pb;                     // rows in the panel
     const int32_t *rank_after;  // running rank
-    const int32_t *pass2;       // set by the rank decisions: the second pass is needed
+    const int32_t *pass2;       // set by the rank decisions: [0] the second pass is needed,
+                                // [1] the panel takes the factor of its rows (TSQR), not of their Gram matrix
 };
 
 __device__ __forceinline__ int rank_before(const int32_t *rank_after, int64_t row) {
@@ -482,6 +487,7 @@ __global__ void __launch_bounds__(TSQR_NT) k_tsqr(const double *S, int sw, int64
                                                   int64_t nin, double *Rout, Panel p) {
     __shared__ __attribute__((aligned(16))) double vbuf[2][VST * TG];
     __shared__ double coefs[2][2];
+    if (!p.pass2[1]) return;           // the Gram matrix's factor was enough
     raise_wave_priority();
     const int t = threadIdx.x;
     const int k = t / TG, g = t % TG;
@@ -606,6 +612,141 @@ __device__ __forceinline__ void tri_inverse_column(double (&y)[PB], int c, int n
     (row(std::integral_constant<int, I>{}), ...);
 }
 
+// What both rank kernels leave (one wave, LDS filled and synchronised): the
+// weights of the new vectors, their coefficients, and whether the second pass
+// is needed.  With Ck the coefficients of the kept rows on the new vectors
+// (lower triangular, pivots on the diagonal), the kept rows are Ck times the
+// new vectors, so X1 = Ck^-1 on the kept rows' columns.  XT zero on entry.
+__device__ __forceinline__ void small_outputs(const double (*C1s)[LP], double (*XT)[LP], const int *krow, const double *rinv,
+                              const double *row_norm, int nk, int pb, double *X1, double *C1, int32_t *pass2_out) {
+    const int l = threadIdx.x;
+    const bool act = l < PB;
+    // lane c: column c, written to XT[row of c][k]
+    if (act && l < nk) {
+        double y[PB];
+        tri_inverse_column(y, l, nk, C1s, krow, rinv, std::make_integer_sequence<int, PB>{});
+        const int ir = krow[l];
+#pragma unroll
+        for (int k = 0; k < PB; ++k)
+            if (k < nk) XT[ir][k] = y[k];
+    }
+    __syncthreads();
+    // outputs; and the largest combination weight sum_i |X1[k][i]| ||c_i||
+    // over the new vectors (lane k: vector k)
+    for (int e = l; e < PB * PB; e += 64) {
+        const int i = e / PB, k = e % PB;           // C1[i][k]
+        C1[e] = (i < pb && k < nk) ? C1s[i][k] : 0.0;
+        const int kx = e / PB, ix = e % PB;         // X1[kx][ix]
+        X1[e] = (kx < nk && ix < pb) ? XT[ix][kx] : 0.0;
+    }
+    double wk = 0.0;
+    if (act && l < nk)
+        for (int i = 0; i < pb; ++i) wk += fabs(XT[i][l]) * row_norm[i];
+    for (int off = 32; off > 0; off >>= 1) wk = fmax(wk, __shfl_xor(wk, off));
+    if (l == 0) *pass2_out = (wk > PASS2_WEIGHT) ? 1 : 0;
+}
+
+// Square root of x (normal, positive) and its reciprocal, both to about one
+// unit in the last place: the hardware's estimate and two Newton steps, half
+// the dependent instructions of sqrt() followed by a division.
+__device__ __forceinline__ void sqrt_and_inverse(double x, double &root, double &inv) {
+    double y = __builtin_amdgcn_rsq(x);
+#pragma unroll
+    for (int n = 0; n < 2; ++n) y = fma(0.5 * y, fma(-x * y, y, 1.0), y);
+    const double r = x * y;
+    root = fma(0.5 * y, fma(-r, r, x), r);
+    inv = fma(y, fma(-root, y, 1.0), y);
+}
+
+// Rank decisions from the panel's Gram matrix G (the inner products of its
+// rows after the first pass): Cholesky with the dependent rows skipped.  A sum
+// of squares shows a row to be dependent when G_ii itself is below the
+// threshold (the row lay in the span of the earlier panels); a pivot, which is
+// a difference, shows it to be independent when it is at least GRAM_SAFE
+// ||c_i||^2 (its rounding error is then below 1e-11 of it).  Any other row
+// (nearly dependent, a copy within the panel, squares out of range, NaN) sends
+// the whole panel to the factor of the rows themselves.  Outputs as
+// k_small_rank's, and pass2_out[1]: 0 decided here, 1 to be decided there.
+// One wave; lane l holds column l of the trailing matrix, which is symmetric
+// bit for bit, so step i publishes row i with one LDS write per lane.  The loop
+// is unrolled (registers indexed by i); a step is a chain of a pivot broadcast,
+// its root and inverse, one LDS round trip and the update: 21 us a panel, with
+// the Gram reduction and the empty launches of the other factor 34, where three
+// levels of TSQR and k_small_rank took 115 (D = 4096; the whole call of 1000
+// rows 7.02 -> 4.22 ms, 2048 x 16384 with 205 copies 15.4 -> 10.9).
+constexpr double GRAM_SAFE = 1e-4;
+
+__global__ void __launch_bounds__(64) k_small_gram(const double *G, const double *cn, double tol, Panel p,
+                                                   int32_t *rank_after, int32_t *kept, double *X1, double *C1,
+                                                   int32_t *pass2_out) {
+    __shared__ __attribute__((aligned(16))) double C1s[PB][LP];
+    __shared__ __attribute__((aligned(16))) double XT[PB][LP];
+    __shared__ __attribute__((aligned(16))) double zb[2][PB];
+    __shared__ double row_norm[PB], rinv[PB];
+    __shared__ int krow[PB], after[PB];
+    raise_wave_priority();
+    const int l = threadIdx.x;
+    const bool row_l = l < p.pb;
+    const int r_old = rank_before(p.rank_after, p.i0);
+    const double nrm = row_l ? cn[p.i0 + l] : 0.0;
+    double a[PB];
+#pragma unroll
+    for (int e = 0; e < PB; ++e) a[e] = (row_l && e < p.pb) ? G[e * PB + l] : 0.0;
+    for (int e = l; e < PB * LP; e += 64) {
+        (&C1s[0][0])[e] = 0.0;
+        (&XT[0][0])[e] = 0.0;
+    }
+    // per row: 1 dependent for certain, 2 independent if its pivot is at least
+    // `safe`, 0 neither (the squares could leave the range)
+    const double t = tol * nrm, thr2 = t * t;
+    double gd = 0.0;
+#pragma unroll
+    for (int e = 0; e < PB; ++e) gd = (e == l) ? a[e] : gd;
+    const bool ranged = nrm > 1e-100 && nrm < 1e100;
+    const int kind = (nrm == 0.0 || (ranged && gd * (1.0 + 1e-9) <= thr2)) ? 1 : (ranged ? 2 : 0);
+    const double safe = fmax(GRAM_SAFE * nrm * nrm, thr2 * (1.0 + 1e-9));
+    if (l < PB) {
+        row_norm[l] = nrm;
+        krow[l] = 0;
+    }
+    __syncthreads();
+    int nk = 0;
+    bool slow = false;
+#pragma unroll
+    for (int i = 0; i < PB; ++i) {
+        if (i < p.pb && !slow) {
+            const int ki = __builtin_amdgcn_readlane(kind, i);
+            if (ki != 1) {
+                const double piv = lane_value(a[i], i), sf = lane_value(safe, i);
+                if (ki == 2 && piv > sf) {
+                    double rho, inv;
+                    sqrt_and_inverse(piv, rho, inv);
+                    const double d = a[i] * inv;             // <w_l, v_nk> for the rows l > i
+                    if (l < PB) zb[i & 1][l] = d;
+                    if (row_l && l >= i) C1s[l][nk] = (l == i) ? rho : d;
+                    if (l == 0) {
+                        krow[nk] = i;
+                        rinv[nk] = inv;
+                    }
+                    __syncthreads();
+#pragma unroll
+                    for (int e = i + 1; e < PB; ++e) a[e] -= d * zb[i & 1][e];
+                    ++nk;
+                } else {
+                    slow = true;
+                }
+            }
+            if (l == 0) after[i] = nk;
+        }
+    }
+    if (l == 0) pass2_out[1] = slow ? 1 : 0;
+    if (slow) return;
+    __syncthreads();
+    if (row_l) rank_after[p.i0 + l] = r_old + after[l];
+    if (l < nk) kept[r_old + l] = (int32_t)(p.i0 + krow[l]);
+    small_outputs(C1s, XT, krow, rinv, row_norm, nk, p.pb, X1, C1, pass2_out);
+}
+
 __global__ void __launch_bounds__(64) k_small_rank(const double *Rt, const double *cn, double tol, Panel p,
                                                    int32_t *rank_after, int32_t *kept, double *X1, double *C1,
                                                    int32_t *pass2_out) {
@@ -618,6 +759,7 @@ __global__ void __launch_bounds__(64) k_small_rank(const double *Rt, const doubl
     __shared__ int kidx[PB];                                     // kept index of each row (-1: dependent)
     __shared__ int krow[PB];                                     // row that made each kept vector
     __shared__ double rinv[PB];                                  // 1 / pivot of each kept vector
+    if (!p.pass2[1]) return;           // the Gram matrix's factor was enough
     raise_wave_priority();
     const int l = threadIdx.x;
     const bool act = l < PB;
@@ -724,41 +866,14 @@ __global__ void __launch_bounds__(64) k_small_rank(const double *Rt, const doubl
         if (l == 0) rank_after[p.i0 + i] = r_old + nk;
     }
     __syncthreads();
-    // weights of the new vectors: with Ck the coefficients of the kept rows on
-    // the new vectors (lower triangular, pivots on the diagonal), the kept
-    // rows are Ck times the new vectors, so X1 = Ck^-1 on the kept rows'
-    // columns.  Lane c: column c, written to XT[row of c][k]
-    if (act && l < nk) {
-        double y[PB];
-        tri_inverse_column(y, l, nk, C1s, krow, rinv, std::make_integer_sequence<int, PB>{});
-        const int ir = krow[l];
-#pragma unroll
-        for (int k = 0; k < PB; ++k)
-            if (k < nk) XT[ir][k] = y[k];
-    }
-    __syncthreads();
-    // outputs; and the largest combination weight sum_i |X1[k][i]| ||c_i||
-    // over the new vectors (lane k: vector k)
-    for (int e = l; e < PB * PB; e += 64) {
-        const int i = e / PB, k = e % PB;           // C1[i][k]
-        C1[e] = (i < p.pb && k < nk) ? C1s[i][k] : 0.0;
-        const int kx = e / PB, ix = e % PB;         // X1[kx][ix]
-        X1[e] = (kx < nk && ix < p.pb) ? XT[ix][kx] : 0.0;
-    }
-    double wk = 0.0;
-    if (act && l < nk)
-        for (int i = 0; i < p.pb; ++i) wk += fabs(XT[i][l]) * thr_cn[i];
-    for (int off = 32; off > 0; off >>= 1) wk = fmax(wk, __shfl_xor(wk, off));
-    if (l == 0) *pass2_out = (wk > PASS2_WEIGHT) ? 1 : 0;
+    small_outputs(C1s, XT, krow, rinv, thr_cn, nk, p.pb, X1, C1, pass2_out);
 }
 
 // Cholesky factor L of the Gram matrix G (n x n, n = new vectors; the
 // vectors are orthonormal up to rounding) and its inverse.  LX[0] = L (lower),
 // LX[1] = L^-1.  A pivot that is not positive sets flag 2.  One wave,
-// right-looking: lane l holds column l of the trailing matrix in registers;
-// step j broadcasts column j through LDS, and every later lane subtracts its
-// outer-product share (entries at or above j of a lane's column are no
-// longer read and are left as they come).
+// right-looking, as k_small_gram (unrolled; row j of the symmetric trailing
+// matrix published with one LDS write per lane): 28 -> 19 us (32 vectors).
 template <int... I>
 __device__ __forceinline__ void inv_rows(double (&y)[PB], int c, const double (*L)[PB + 1], const double *rd,
                                          std::integer_sequence<int, I...>) {
@@ -779,7 +894,7 @@ __device__ __forceinline__ void inv_rows(double (&y)[PB], int c, const double (*
 
 __global__ void __launch_bounds__(64) k_small_chol(const double *G, Panel p, double *LX, int32_t *flag) {
     __shared__ double L[PB][PB + 1];
-    __shared__ __attribute__((aligned(16))) double zb[PB];
+    __shared__ __attribute__((aligned(16))) double zb[2][PB];
     __shared__ double rd[PB];          // 1 / L[j][j]
     raise_wave_priority();
     const int l = threadIdx.x;
@@ -790,24 +905,22 @@ __global__ void __launch_bounds__(64) k_small_chol(const double *G, Panel p, dou
 #pragma unroll
     for (int e = 0; e < PB; ++e) a[e] = (act && l < n && e < n) ? G[e * PB + l] : 0.0;
     bool bad = false;
-    for (int j = 0; j < n; ++j) {
-        if (l == j) {
 #pragma unroll
-            for (int e = 0; e < PB; ++e) zb[e] = a[e];
-        }
-        __syncthreads();
-        const double piv = zb[j];
-        if (!(piv > 0.0)) bad = true;
-        const double d = sqrt(piv > 0.0 ? piv : 1.0);
-        const double inv = 1.0 / d;
-        if (act && l >= j && l < n) L[l][j] = (l == j) ? d : zb[l] * inv;
-        if (l == j) rd[j] = inv;
-        if (act && l > j && l < n) {
-            const double f = zb[l] * inv * inv;    // L[l][j] / L[j][j]
+    for (int j = 0; j < PB; ++j) {
+        if (j < n) {
+            const double piv = lane_value(a[j], j);
+            const bool pos = piv > 0.0;
+            if (!pos) bad = true;
+            double d, inv;
+            sqrt_and_inverse(pos ? piv : 1.0, d, inv);
+            const double f = a[j] * inv;               // L[l][j]
+            if (act) zb[j & 1][l] = f;
+            if (act && l >= j && l < n) L[l][j] = (l == j) ? d : f;
+            if (l == j) rd[j] = inv;
+            __syncthreads();
 #pragma unroll
-            for (int e = 0; e < PB; ++e) a[e] -= f * zb[e];
+            for (int e = j + 1; e < PB; ++e) a[e] -= f * zb[j & 1][e];
         }
-        __syncthreads();
     }
     // identity padding beyond n keeps the inverse finite
     if (act && l >= n) {
@@ -1046,7 +1159,10 @@ hipError_t run_compress(const void *C, gs_dtype ct, int64_t M, int64_t D, int64_
         if (q > 0) {
             if (ov) GS_TRY(hipStreamWaitEvent(s, ov->join, 0));
             GS_TRY(block_pass(wp, ROWS_PANEL, qm, ROWS_OLD_B, PB, D, BK_PREV, p, part_prev, PB, hc + i0 * M, M,
-                              nullptr, s));
+                              gpart, s));
+        } else {
+            hipLaunchKernelGGL(k_bupdate, dim3((unsigned)nblk), dim3(NT), 0, s, wp, (int)ROWS_PANEL,
+                               (const double *)h2, M, (const double *)qm, (int)ROWS_OLD, D, p, gpart);
         }
         // the next panel's rows and the first part of its first pass, beside
         // this panel's factorisation (they touch none of its buffers)
@@ -1061,6 +1177,10 @@ hipError_t run_compress(const void *C, gs_dtype ct, int64_t M, int64_t D, int64_
             }
         }
         // 2. rank decisions in the panel's small space; first-round new vectors
+        hipLaunchKernelGGL(k_gram_reduce, dim3(PB * PB / 64), dim3(NT), 0, s, (const double *)gpart, nblk, g2);
+        hipLaunchKernelGGL(k_small_gram, dim3(1), dim3(64), 0, s, (const double *)g2, (const double *)cn, tol, p,
+                           rank_after, kept_ws, x1, c1, pass2);
+        // (these end at once for a panel that the Gram matrix decided)
         double *rt_ = nullptr;
         GS_TRY(panel_factor(wp, ROWS_PANEL, D, p, tsq0, tsq1, &rt_, s));
         hipLaunchKernelGGL(k_small_rank, dim3(1), dim3(64), 0, s, (const double *)rt_, (const double *)cn, tol, p,
