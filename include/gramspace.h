@@ -134,9 +134,11 @@ size_t gs_compress_workspace(int64_t M, int64_t D);
  * Builds an orthonormal basis Q of the row space of the codebook C and its
  * coordinates R with C = R Q, by block Gram-Schmidt with re-orthogonalisation
  * over panels of codebook rows, in fp64 (the rows of a panel are
- * orthogonalised among themselves in the space of the panel's triangular
- * factor, by modified Gram-Schmidt with a second projection wherever the
- * first took away most of a row's norm).  Codebook rows are taken in index
+ * orthogonalised among themselves by the Cholesky factor of their Gram matrix
+ * where its rounding can neither change a rank decision nor cost
+ * orthogonality, otherwise in the space of the panel's triangular factor, by
+ * modified Gram-Schmidt with a second projection wherever the first took away
+ * most of a row's norm).  Codebook rows are taken in index
  * order; row i is dependent (adds no basis vector) when the norm of its part
  * outside the current span is <= tol * ||c_i||.  Kept rows
  * are listed in `kept`, so basis vector k comes from codebook row kept[k].  R

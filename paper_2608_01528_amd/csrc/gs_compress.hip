@@ -16,9 +16,10 @@
 //     same bit for bit);
 //  2. the rows of the panel are orthogonalised among themselves in a small
 //     space.  Where every row is clearly dependent (its norm is below the
-//     threshold already) or clearly independent (its pivot is not small against
-//     ||c_i||), that is the Cholesky factor of the panel's Gram matrix: two
-//     short kernels.  A panel with any other row takes the triangular factor
+//     threshold already) or independent with pivots that the rounding of the
+//     whole factor cannot have made (see k_small_gram), that is the Cholesky
+//     factor of the panel's Gram matrix: two short kernels.  Any other panel
+//     takes the triangular factor
 //     of the panel itself (no squares): W^T = Q_t R_t by a tree of
 //     Householder factorisations (TSQR), so the columns a_i of R_t have the
 //     inner products of the rows w_i.  Modified Gram-Schmidt runs on those
@@ -613,12 +614,14 @@ __device__ __forceinline__ void tri_inverse_column(double (&y)[PB], int c, int n
 }
 
 // What both rank kernels leave (one wave, LDS filled and synchronised): the
-// weights of the new vectors, their coefficients, and whether the second pass
-// is needed.  With Ck the coefficients of the kept rows on the new vectors
-// (lower triangular, pivots on the diagonal), the kept rows are Ck times the
-// new vectors, so X1 = Ck^-1 on the kept rows' columns.  XT zero on entry.
-__device__ __forceinline__ void small_outputs(const double (*C1s)[LP], double (*XT)[LP], const int *krow, const double *rinv,
-                              const double *row_norm, int nk, int pb, double *X1, double *C1, int32_t *pass2_out) {
+// weights of the new vectors and their coefficients.  With Ck the coefficients
+// of the kept rows on the new vectors (lower triangular, pivots on the
+// diagonal), the kept rows are Ck times the new vectors, so X1 = Ck^-1 on the
+// kept rows' columns.  XT zero on entry.  Returns the combination weight
+// sum_i |X1[k][i]| ||c_i|| of new vector k in lane k (0 past the new vectors).
+__device__ __forceinline__ double small_outputs(const double (*C1s)[LP], double (*XT)[LP], const int *krow,
+                                                const double *rinv, const double *row_norm, int nk, int pb,
+                                                double *X1, double *C1) {
     const int l = threadIdx.x;
     const bool act = l < PB;
     // lane c: column c, written to XT[row of c][k]
@@ -631,8 +634,6 @@ __device__ __forceinline__ void small_outputs(const double (*C1s)[LP], double (*
             if (k < nk) XT[ir][k] = y[k];
     }
     __syncthreads();
-    // outputs; and the largest combination weight sum_i |X1[k][i]| ||c_i||
-    // over the new vectors (lane k: vector k)
     for (int e = l; e < PB * PB; e += 64) {
         const int i = e / PB, k = e % PB;           // C1[i][k]
         C1[e] = (i < pb && k < nk) ? C1s[i][k] : 0.0;
@@ -642,8 +643,7 @@ __device__ __forceinline__ void small_outputs(const double (*C1s)[LP], double (*
     double wk = 0.0;
     if (act && l < nk)
         for (int i = 0; i < pb; ++i) wk += fabs(XT[i][l]) * row_norm[i];
-    for (int off = 32; off > 0; off >>= 1) wk = fmax(wk, __shfl_xor(wk, off));
-    if (l == 0) *pass2_out = (wk > PASS2_WEIGHT) ? 1 : 0;
+    return wk;
 }
 
 // Square root of x (normal, positive) and its reciprocal, both to about one
@@ -661,12 +661,22 @@ __device__ __forceinline__ void sqrt_and_inverse(double x, double &root, double 
 // Rank decisions from the panel's Gram matrix G (the inner products of its
 // rows after the first pass): Cholesky with the dependent rows skipped.  A sum
 // of squares shows a row to be dependent when G_ii itself is below the
-// threshold (the row lay in the span of the earlier panels); a pivot, which is
-// a difference, shows it to be independent when it is at least GRAM_SAFE
-// ||c_i||^2 (its rounding error is then below 1e-11 of it).  Any other row
-// (nearly dependent, a copy within the panel, squares out of range, NaN) sends
-// the whole panel to the factor of the rows themselves.  Outputs as
-// k_small_rank's, and pass2_out[1]: 0 decided here, 1 to be decided there.
+// threshold (the row lay in the span of the earlier panels).  A pivot, which is
+// a difference, shows it to be independent only while the rounding of the
+// factor so far is small against it.  The computed factor is the exact one of
+// G + E with |E_ij| <= g ||c_i|| ||c_j||, g a few times 2^-53 (the sums of G
+// included), so the pivot of new vector k, made with the weights X1[k], is off
+// by at most g (sum_i |X1[k][i]| ||c_i||)^2 of itself, and against the factor
+// of G itself by PB times that: below 1e-8 when every weight is at most
+// GRAM_WEIGHT (g = 1e-14 to 4e-14 up to D = 16384).  Pivots alone do not show
+// it: each row of a chain c_i = v_(i-1) + a v_i passes any fixed threshold on
+// them while the errors grow by 1 / a from row to row.  A panel with a larger
+// weight, a row between the two (nearly dependent, a copy within the panel),
+// squares out of range or NaN goes to the factor of the rows themselves.  (Of
+// codebooks with random, binary, cumulated or level-coded rows no panel has a
+// weight above 30 up to M = D / 2; at M = D the last one may.)
+// Outputs as k_small_rank's, and pass2_out[1]: 0 decided here, 1 to be decided
+// there.
 // One wave; lane l holds column l of the trailing matrix, which is symmetric
 // bit for bit, so step i publishes row i with one LDS write per lane.  The loop
 // is unrolled (registers indexed by i); a step is a chain of a pivot broadcast,
@@ -674,7 +684,9 @@ __device__ __forceinline__ void sqrt_and_inverse(double x, double &root, double 
 // the Gram reduction and the empty launches of the other factor 34, where three
 // levels of TSQR and k_small_rank took 115 (D = 4096; the whole call of 1000
 // rows 7.02 -> 4.22 ms, 2048 x 16384 with 205 copies 15.4 -> 10.9).
-constexpr double GRAM_SAFE = 1e-4;
+constexpr double GRAM_WEIGHT = 100.0;
+constexpr double GRAM_SAFE = 1.0 / (GRAM_WEIGHT * GRAM_WEIGHT);   // a pivot below this share has a larger weight
+constexpr double GRAM_MARGIN = 1.0 + 1e-6;                        // of a pivot to the threshold
 
 __global__ void __launch_bounds__(64) k_small_gram(const double *G, const double *cn, double tol, Panel p,
                                                    int32_t *rank_after, int32_t *kept, double *X1, double *C1,
@@ -704,7 +716,7 @@ __global__ void __launch_bounds__(64) k_small_gram(const double *G, const double
     for (int e = 0; e < PB; ++e) gd = (e == l) ? a[e] : gd;
     const bool ranged = nrm > 1e-100 && nrm < 1e100;
     const int kind = (nrm == 0.0 || (ranged && gd * (1.0 + 1e-9) <= thr2)) ? 1 : (ranged ? 2 : 0);
-    const double safe = fmax(GRAM_SAFE * nrm * nrm, thr2 * (1.0 + 1e-9));
+    const double safe = fmax(GRAM_SAFE * nrm * nrm, thr2 * GRAM_MARGIN);
     if (l < PB) {
         row_norm[l] = nrm;
         krow[l] = 0;
@@ -739,12 +751,18 @@ __global__ void __launch_bounds__(64) k_small_gram(const double *G, const double
             if (l == 0) after[i] = nk;
         }
     }
+    __syncthreads();
+    if (!slow) {
+        // (X1 and C1 are written again by k_small_rank when it decides)
+        const double wk = small_outputs(C1s, XT, krow, rinv, row_norm, nk, p.pb, X1, C1);
+        const int second = __any(wk > PASS2_WEIGHT);
+        if (l == 0) pass2_out[0] = second;
+        slow = __any(!(wk <= GRAM_WEIGHT));
+    }
     if (l == 0) pass2_out[1] = slow ? 1 : 0;
     if (slow) return;
-    __syncthreads();
     if (row_l) rank_after[p.i0 + l] = r_old + after[l];
     if (l < nk) kept[r_old + l] = (int32_t)(p.i0 + krow[l]);
-    small_outputs(C1s, XT, krow, rinv, row_norm, nk, p.pb, X1, C1, pass2_out);
 }
 
 __global__ void __launch_bounds__(64) k_small_rank(const double *Rt, const double *cn, double tol, Panel p,
@@ -866,7 +884,9 @@ __global__ void __launch_bounds__(64) k_small_rank(const double *Rt, const doubl
         if (l == 0) rank_after[p.i0 + i] = r_old + nk;
     }
     __syncthreads();
-    small_outputs(C1s, XT, krow, rinv, thr_cn, nk, p.pb, X1, C1, pass2_out);
+    const double wk = small_outputs(C1s, XT, krow, rinv, thr_cn, nk, p.pb, X1, C1);
+    const int second = __any(wk > PASS2_WEIGHT);
+    if (l == 0) pass2_out[0] = second;
 }
 
 // Cholesky factor L of the Gram matrix G (n x n, n = new vectors; the
