@@ -479,7 +479,8 @@ __device__ __forceinline__ void mma_256(const GemmArgs &g, const TileLoads<T, BN
 // What bounds it is power: the matrix cores are busy 59 % of the time at 1.83
 // GHz (bf16 operands: 73 % at 1.42).  65536 x 256 x 8192 (project): 1.94 ms with
 // fp32 MFMAs, 1.48 now; 16384 x 1000 x 4096: 970 -> 747 us; the error against 64
-// bits of these results 1.4e-6 -> 6.4e-7 and 1.5e-6 -> 3.7e-7.  With the
+// bits of these results 1.4e-6 -> 3.6e-7 and 1.5e-6 -> 3.7e-7 (||x||^2 of the
+// first, summed beside it, 3.0e-7 -> 2.2e-7).  With the
 // six products added straight to the running sums it is 7 % faster, but
 // positive sums (a binary codebook's) then round further off than in fp32
 // (1.6e-6).
@@ -561,8 +562,11 @@ __device__ __forceinline__ bool mma_256_planes(const GemmArgs &g, int64_t m0, in
             for (int e = 0; e < 8; ++e) v[e] = (k + e < kend) ? v[e] : 0.f;
         }
         if (sum) {
+            // (the eight squares first: one rounding of the long sum per K-step)
+            float t = v[0] * v[0];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) n += v[e] * v[e];
+            for (int e = 1; e < 8; ++e) t += v[e] * v[e];
+            n += t;
         }
         u32x4 p[3];
         split8(v, p);

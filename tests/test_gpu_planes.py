@@ -89,3 +89,20 @@ def test_planes_infinities_and_nan():
     keep = torch.ones(B, dtype=torch.bool, device="cuda")
     keep[7] = keep[300] = False
     assert torch.all(((T.double() - x @ q.T).abs() <= bound(x, q.T, K))[keep])
+
+
+def test_planes_row_norms_rounding():
+    """||x||^2 beside the product: a thread sums K / 2 squares, eight of a
+    K-step first, so the long sum is rounded n = K / 16 times.  A rounding is
+    2^-24 / sqrt(3) of the sum so far at most, in the root mean square, and
+    the sum grows evenly: 2^-24 sqrt(n) / 3 for a half, less for both."""
+    gs = _gs()
+    K = 8192
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    X = torch.randn(16384, K, generator=g, device="cuda")
+    Q = torch.randn(2048, K, generator=g, device="cuda")
+    _, n2 = gs.gs_project(X, Q, xnorm2=True)
+    exact = torch.cat([x.double().square().sum(1) for x in X.split(4096)])
+    rel = (n2.double() - exact) / exact
+    assert rel.square().mean().sqrt() <= 2.0 ** -24 * (K / 16) ** 0.5 / 3
