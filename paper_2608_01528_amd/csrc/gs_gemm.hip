@@ -1,5 +1,5 @@
 // Dense contractions of the Gram-Space operators on CDNA4 matrix cores: the
-// choice between the tile kernels (launch_gemm, below), the 128 x 128 tiles
+// choice between the tile kernels (product_route, below), the 128 x 128 tiles
 // for operands the others don't take (two element types, fewer than 16 bytes
 // of K, strides beyond their 32-bit offsets) and the argmax-only row sweep.
 //
@@ -1010,28 +1010,85 @@ hipError_t raise_lds_limit(const void *kernel, size_t lds) {
     return e;
 }
 
+namespace {
+
+// Operands of one type, every row 16-byte aligned: the asynchronous-load loops.
+bool rows_aligned(gs_dtype ta, gs_dtype tb, Epi epi, const GemmArgs &a) {
+    const int64_t per = (ta == GS_BF16) ? 8 : 4;
+    auto rows16 = [&](const void *p, int64_t ld) { return aligned16(p) && ld % per == 0; };
+    return ta == tb && rows16(a.A, a.lda) && rows16(a.B, a.ldb) && (epi != EPI_BIND || rows16(a.A2, a.lda2));
+}
+
+}  // namespace
+
+Route product_route(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi epi, const GemmArgs &a) {
+    const bool rows_ok = rows_aligned(ta, tb, epi, a), sm = epi == EPI_SOFTMAX;
+    const bool stores = epi == EPI_STORE || epi == EPI_BIND;
+    const bool scores = !b_nn && (sm || (epi == EPI_SIM && a.write_out));      // written to memory
+    if (stores || scores) {
+        // a few scores: one per work-group, its threads sharing the K range
+        if (scores && ta == tb && few_scores(a.M, a.N)) return ROUTE_FEW_ROWS;
+        // 256 x 256 tiles where they fill the CUs, small tiles that share out
+        // the K range where they don't
+        bool large = rows_ok && (epi != EPI_BIND || tout == GS_F32) && gemm256_fits(ta, a, b_nn);
+        if (ta == tb && split_takes(ta, b_nn, epi, a)) {
+            // (where the large tiles can't take the operands, the small ones
+            // are the faster of the two left at every size.  128 x 128 and
+            // small tiles, us: bf16 bound product 16384 x 1000 x 4096 636,
+            // 585, 65536 x 256 x 8192 1655, 1300; unaligned rows, project
+            // 65536 x 8191 x 256 fp32 4416, 2335, bf16 1830, 808; 512 x 4095 x
+            // 360 fp32 541, 24; restore 16384 x 999 x 4095 fp32 1963, 1199,
+            // bf16 920, 373; scores 16384 x 901 x 999 fp32 518, 289)
+            if (!large || split_better(ta, b_nn, epi, a)) return ROUTE_SPLIT;
+        } else {
+            // less than 16 bytes of K (or strides of 2^22): nothing to share
+            // out.  Up to 64 large tiles the 128 x 128 ones make one round of
+            // the CUs and shorter work-groups; with bf16 output the large ones
+            // are the faster there where no tile is cut, and slower up to
+            // their own full round where columns are (element stores).  128 x
+            // 128 and 256 x 256 tiles, us, K = 3 fp32, 7 bf16: scores 64 x 256
+            // fp32 10.0, 16.2; 4096 x 1000 12.5, 21.1; 9000 x 1000 24.0, 22.4;
+            // restore 2048 x 2048 fp32 9.6, 11.3, bf16 10.8, 9.2; 4096 x 2048
+            // 13.1, 12.1 and 20.3, 9.8; 1000 x 1000 bf16 10.0, 27.7; 9000 x
+            // 1000 28.2, 29.8; 20000 x 256 19.2, 10.0
+            const int64_t tiles = ((a.M + 255) / 256) * ((a.N + 255) / 256);
+            if (tout == GS_BF16) large = large && (tiles >= 256 || (a.N % 256 == 0 && (a.M % 256 == 0 || tiles > 64)));
+            else large = large && tiles > 64;
+        }
+        return large ? ROUTE_TILES256 : ROUTE_TILES128;
+    }
+    // argmax alone: whole rows in one tile (the row results come from the
+    // product's epilogue), or a sweep over 256-row blocks, where a round of
+    // them fills the CUs
+    if (!b_nn && rows_ok && sweep256_fits(ta, a))
+        return (a.N <= 256 && gemm256_fits(ta, a, false)) ? ROUTE_TILES256 : ROUTE_SWEEP256;
+    return ROUTE_SWEEP128;
+}
+
+// The route of a product with rows at `ld` elements from 16-byte aligned
+// addresses, for tests of the choice: host only, nothing is read or launched.
+extern "C" int gs_test_product_route(int type, int type_out, int b_nn, int epi, int64_t M, int64_t N, int64_t K,
+                                     int64_t lda, int64_t ldb, int write_out, int argmax) {
+    GemmArgs a{};
+    a.M = M; a.N = N; a.K = K; a.lda = a.lda2 = lda; a.ldb = ldb; a.write_out = write_out;
+    static int32_t some;
+    a.argmax = argmax ? &some : nullptr;
+    return product_route((gs_dtype)type, (gs_dtype)type, (gs_dtype)type_out, b_nn, (Epi)epi, a);
+}
+
 hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi epi,
                        const GemmArgs &a_in, hipStream_t s) {
     if (a_in.M == 0 || a_in.N == 0) return hipSuccess;
     GemmArgs a = a_in;
-    // asynchronous-load loops: operands of one type, every row 16-byte aligned
-    const bool same = (ta == GS_BF16 && tb == GS_BF16) || (ta == GS_F32 && tb == GS_F32);
-    const int64_t per = (ta == GS_BF16) ? 8 : 4;
-    auto rows16 = [&](const void *p, int64_t ld) { return aligned16(p) && ld % per == 0; };
-    const bool rows_ok = same && rows16(a.A, a.lda) && rows16(a.B, a.ldb) &&
-                         (epi != EPI_BIND || rows16(a.A2, a.lda2));
-    a.dma = rows_ok && ta == GS_BF16;   // the 128 x 128 pipelined loop is bf16 only
+    a.dma = ta == GS_BF16 && rows_aligned(ta, tb, epi, a);   // the 128 x 128 pipelined loop is bf16 only
     const bool sm = epi == EPI_SOFTMAX;
-    const bool stores = epi == EPI_STORE || epi == EPI_BIND;
-    const bool scores = !b_nn && (sm || (epi == EPI_SIM && a.write_out));      // written to memory
-    // a few scores: one per work-group, its threads sharing the K range
-    if (scores && ta == tb && few_scores(a.M, a.N)) return launch_few_rows(ta, a, sm, s);
-    // 256 x 256 tiles where they fill the CUs, small tiles that share out the
-    // K range where they don't
-    const bool large = rows_ok && (epi != EPI_BIND || tout == GS_F32) && gemm256_fits(ta, a, b_nn);
-    if (same && (stores || scores) && split_fits(ta, b_nn, epi, a, large)) return launch_split(ta, tout, b_nn, epi, a, s);
-    if (epi == EPI_STORE && large) return launch_gemm256(ta, tout, b_nn, a, s);
-    if (epi == EPI_BIND && large) {
+    const Route route = product_route(ta, tb, tout, b_nn, epi, a);
+    if (route == ROUTE_FEW_ROWS) return launch_few_rows(ta, a, sm, s);
+    if (route == ROUTE_SPLIT) return launch_split(ta, tout, b_nn, epi, a, s);
+    if (route == ROUTE_SWEEP256) return launch_sweep256(ta, sm, a, s);
+    if (route == ROUTE_TILES256 && (epi == EPI_SIM || sm)) return launch_scores256(ta, a, sm, s);
+    if (route == ROUTE_TILES256 && epi == EPI_STORE) return launch_gemm256(ta, tout, b_nn, a, s);
+    if (route == ROUTE_TILES256) {
         // bound product on the large tiles: X = T Q, then X = X .* (T2 Q) in
         // the second product's epilogue (fp32 X holds the first factor exactly)
         GemmArgs first = a, second = a;
@@ -1058,17 +1115,9 @@ hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi e
         if (!bf_a && bf_b && bf_o) return dispatch_store<float, bf16_t, bf16_t>(b_nn, bind, a, veca, vecb, s);
         return hipErrorInvalidValue;
     }
-    if (scores && large) return launch_scores256(ta, a, sm, s);
-    // argmax alone: whole rows in one tile (the row results come from the
-    // product's epilogue), or a sweep over 256-row blocks, where a round of
-    // them fills the CUs
-    if (!b_nn && rows_ok && sweep256_fits(ta, a)) {
-        if (a.N <= 256 && gemm256_fits(ta, a, false)) return launch_scores256(ta, a, sm, s);
-        return launch_sweep256(ta, sm, a, s);
-    }
     // scores or weights written anyway: product with a scaled epilogue, then
     // the row pass; argmax alone: the row sweep (no score matrix in memory)
-    if (scores) {
+    if (route == ROUTE_TILES128) {
         if (!bf_a && !bf_b) return dispatch_scores<float, float>(sm, a, veca, vecb, s);
         if (bf_a && bf_b) return dispatch_scores<bf16_t, bf16_t>(sm, a, veca, vecb, s);
     }

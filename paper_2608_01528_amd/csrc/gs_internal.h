@@ -128,6 +128,18 @@ struct GemmArgs {
 hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi epi,
                        const GemmArgs &a, hipStream_t s);
 
+// Kernels a product takes, chosen by launch_gemm from sizes, types and
+// alignment alone.
+enum Route {
+    ROUTE_FEW_ROWS = 0,     // a work-group per score
+    ROUTE_SPLIT = 1,        // small tiles, the K range of a tile shared by waves
+    ROUTE_TILES256 = 2,     // 256 x 256 tiles
+    ROUTE_SWEEP256 = 3,     // argmax alone, 256-row blocks
+    ROUTE_TILES128 = 4,     // 128 x 128 tiles
+    ROUTE_SWEEP128 = 5      // argmax alone, 128-row blocks
+};
+Route product_route(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi epi, const GemmArgs &a);
+
 // 256 x 256-tile product with a plain store (and optional row norms of A),
 // both operands of type t (bf16 or fp32) with 16-byte aligned rows.
 // gemm256_fits tells whether their 32-bit offsets reach the operands.
@@ -135,10 +147,11 @@ bool gemm256_fits(gs_dtype t, const GemmArgs &a, bool b_nn);
 hipError_t launch_gemm256(gs_dtype t, gs_dtype tout, bool b_nn, const GemmArgs &a, hipStream_t s);
 // Products with few output tiles (request-sized batches): small tiles, the K
 // range of a tile dealt to the waves of its work-group.  Both operands of type
-// t; EPI_SIM must write its scores (the row pass follows).  split_fits tells
-// whether the operands allow these tiles and, where the 256 x 256 tiles are
-// possible too (large_tiles), which of the two are the better ones.
-bool split_fits(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a, bool large_tiles);
+// t; EPI_SIM must write its scores (the row pass follows).  split_takes tells
+// whether the operands allow these tiles, split_better whether they are then
+// faster than the 256 x 256 ones.
+bool split_takes(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a);
+bool split_better(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a);
 hipError_t launch_split(gs_dtype t, gs_dtype tout, bool b_nn, Epi epi, const GemmArgs &a, hipStream_t s);
 // Row sweep of similarity (softmax = false) or attention scores over 256 x
 // 256 blocks, same operand conditions (B stored N x K).

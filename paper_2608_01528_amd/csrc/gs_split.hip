@@ -586,10 +586,14 @@ bool make_plan(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a, Plan &p) {
 
 }  // namespace
 
-bool split_fits(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a, bool large_tiles) {
+bool split_takes(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a) {
+    Plan p;
+    return make_plan(t, b_nn, epi, a, p);
+}
+
+bool split_better(gs_dtype t, bool b_nn, Epi epi, const GemmArgs &a) {
     Plan p;
     if (!make_plan(t, b_nn, epi, a, p)) return false;
-    if (!large_tiles) return true;
     const int64_t es = t == GS_BF16 ? 2 : 4;
     const LargeModel m = es == 2 ? BF16_LARGE : F32_LARGE;
     const double rounds = (double)((tiles_of(a, 256, 256) + 255) / 256), step = m.per_step * (double)((a.K * es + 127) / 128);

@@ -171,3 +171,33 @@ def test_scores_with_norms_summed_in_their_own_pass(dtype, r):
     assert np.all(np.abs(g - exact) <= bound)
     assert torch.equal(i1.long(), S1.argmax(1)) or torch.all(S1.gather(1, i1.long()[:, None])[:, 0] == S1.amax(1))
     assert int(i1[5]) == 0 and torch.all(S1[5] == 0)
+
+
+@pytest.mark.parametrize("layout", ["aligned", "odd"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("rows,K,cols", [(64, 3, 100), (1000, 7, 200), (70, 1, 33), (300, 2, 2)])
+def test_short_k(rows, K, cols, dtype, layout):
+    """Fewer than 16 bytes of K or of a row of B (128 x 128 tiles; K = 7 in
+    fp32: small ones)."""
+    gs = _gs()
+    X, x = operand(rows, K, dtype, 21, layout)
+    Y, y = operand(rows, K, dtype, 22, layout)
+    Q, q = operand(cols, K, dtype, 23, layout)
+    B, b = operand(K, cols, dtype, 24, layout)
+    for ot in (torch.float32, torch.bfloat16):
+        buf, out = output(rows, cols, ot, layout)
+        _, n2 = gs.gs_project(X, Q, out=out, xnorm2=True)
+        check(buf, out, x @ q.T, product_bound(x, q.T, K, ot), cols)
+        n64 = (x * x).sum(1)
+        assert np.all(np.abs(n2.cpu().double().numpy() - n64) <= gamma(K + 8) * n64)
+        buf, out = output(rows, cols, ot, layout)
+        gs.gs_reconstruct(X, B, out=out)
+        check(buf, out, x @ b, product_bound(x, b, K, ot), cols)
+        buf, out = output(rows, cols, ot, layout)
+        gs.gs_reconstruct(X, B, T2=Y, bind="mul", out=out)
+        e1, e2 = (product_bound(a, b, K, torch.float32) for a in (x, y))
+        lim = e1 * np.abs(y @ b) + e2 * np.abs(x @ b) + e1 * e2
+        check(buf, out, (x @ b) * (y @ b), lim + U_OUT[ot] * 1.01 * np.abs((x @ b) * (y @ b)) + 1e-30, cols)
+    buf, S = output(rows, cols, torch.float32, layout)
+    gs.gs_similarity(X, Q, mode="dot", out=S, argmax=False)
+    check(buf, S, x @ q.T, product_bound(x, q.T, K, torch.float32), cols)
