@@ -15,6 +15,7 @@ import torch
 import oracle
 from paper_2608_01528_amd import gramspace as gsm
 from paper_2608_01528_amd import workloads as wl
+from tests import test_product_routes as routes
 from tests.gpu_util import (TOL_BF16, TOL_F32, U32, check_argmax_bound, dev, exact_scores_bound, gamma, host,
                             rowrel, score_bound, cosine_factor)
 
@@ -980,9 +981,18 @@ def test_bf16_pipelined_prob2vec_similarity(B, M, D):
 # 16-byte chunk, NaN-filled row padding, and both output types.  Q and R are
 # arbitrary here: project, prob2vec and reconstruct are plain products of
 # their operands.  Rows are sampled: the first and last, the tile boundaries
-# and random rows.
+# and random rows.  The smaller size of each test is one that fp32 (the short
+# restores in both types) runs on small tiles; the larger takes the 256 x 256
+# ones, as `takes` asserts.
 
 OP_DTYPES = [torch.bfloat16, torch.float32]
+
+
+def takes(large, form, rows, cols, K, op_dtype, out_dtype=None):
+    """The product takes the 256 x 256 tiles, or (not large) may take others."""
+    ty = {torch.float32: routes.F32, torch.bfloat16: routes.BF16}
+    got = routes.route(form, rows, cols, K, ty[op_dtype], ty[out_dtype or op_dtype])
+    assert got == routes.TILES256 or not large, (form, rows, cols, K, got)
 
 
 def _tile_rows(B, seed):
@@ -1015,10 +1025,10 @@ def _name(dt):
 
 
 @pytest.mark.parametrize("op_dtype", OP_DTYPES, ids=_name)
-@pytest.mark.parametrize("D", [300, 4100])
+@pytest.mark.parametrize("B,r,D", [(8200, 2000, 300), (8200, 2000, 4100), (16300, 2030, 300), (16300, 2030, 1100)])
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16], ids=_name)
-def test_large_tile_project(op_dtype, D, out_dtype):
-    B, r = 8200, 2000
+def test_large_tile_project(op_dtype, B, r, D, out_dtype):
+    takes(B > 8200, routes.PROJECT, B, r, D, op_dtype, out_dtype)
     print("large-tile project", _name(op_dtype), B, D, r, _name(out_dtype), flush=True)
     X, Q = _mat(B, D, 1, op_dtype), _mat(r, D, 2, op_dtype, 1 / np.sqrt(D))
     ld = _ld(D, op_dtype)
@@ -1035,8 +1045,9 @@ def test_large_tile_project(op_dtype, D, out_dtype):
 
 @pytest.mark.parametrize("op_dtype", OP_DTYPES, ids=_name)
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16], ids=_name)
-def test_large_tile_reconstruct(op_dtype, out_dtype):
-    B, r, D = 2100, 45, 7700
+@pytest.mark.parametrize("B,r,D", [(2100, 45, 7700), (4090, 45, 7700)])
+def test_large_tile_reconstruct(op_dtype, out_dtype, B, r, D):
+    takes(B > 2100, routes.RESTORE, B, D, r, op_dtype, out_dtype)
     print("large-tile reconstruct", _name(op_dtype), B, r, D, _name(out_dtype), flush=True)
     T, Q = _mat(B, r, 4, op_dtype), _mat(r, D, 5, op_dtype)
     X = gsm.gs_reconstruct(nan_padded(T, _ld(r, op_dtype), op_dtype), nan_padded(Q, _ld(D, op_dtype, 8), op_dtype),
@@ -1053,10 +1064,11 @@ def test_large_tile_reconstruct(op_dtype, out_dtype):
 
 @pytest.mark.parametrize("op_dtype", OP_DTYPES, ids=_name)
 @pytest.mark.parametrize("out_dtype", [torch.float32, torch.bfloat16], ids=_name)
-def test_large_tile_bind(op_dtype, out_dtype):
+@pytest.mark.parametrize("B,r,D", [(2100, 45, 7700), (8190, 45, 7900)])
+def test_large_tile_bind(op_dtype, out_dtype, B, r, D):
     # X = (T Q) .* (T2 Q): with an fp32 output the large-tile path forms the
     # two products one after the other, the second multiplied into the first
-    B, r, D = 2100, 45, 7700
+    takes(B > 2100 and out_dtype == torch.float32, routes.BIND, B, D, r, op_dtype, out_dtype)
     print("large-tile bind", _name(op_dtype), B, r, D, _name(out_dtype), flush=True)
     T, T2, Q = _mat(B, r, 31, op_dtype), _mat(B, r, 32, op_dtype), _mat(r, D, 33, op_dtype)
     ldr, ldd = _ld(r, op_dtype), _ld(D, op_dtype, 8)
@@ -1074,8 +1086,9 @@ def test_large_tile_bind(op_dtype, out_dtype):
 
 
 @pytest.mark.parametrize("op_dtype", OP_DTYPES, ids=_name)
-def test_large_tile_prob2vec(op_dtype):
-    B, M, r = 8200, 2050, 2000
+@pytest.mark.parametrize("B,M,r", [(8200, 2050, 2000), (16300, 2050, 2030)])
+def test_large_tile_prob2vec(op_dtype, B, M, r):
+    takes(B > 8200, routes.RESTORE, B, r, M, op_dtype, torch.float32)
     print("large-tile prob2vec", _name(op_dtype), B, M, r, flush=True)
     P = wl.dirichlet_probs(B, M, 0.5, 7)
     if op_dtype == torch.bfloat16:
@@ -1100,6 +1113,8 @@ def test_large_tile_prob2vec(op_dtype):
 @pytest.mark.parametrize("op_dtype", OP_DTYPES, ids=_name)
 def test_persistent_tile_walk(op_dtype):
     B, K, N = 16384, 300, 2048
+    for form in (routes.PROJECT, routes.RESTORE, routes.BIND):
+        takes(True, form, B, N, K, op_dtype, torch.float32)
     print("persistent tile walk", _name(op_dtype), B, K, N, flush=True)
     X, Q = _mat(B, K, 81, op_dtype), _mat(N, K, 82, op_dtype, 1 / np.sqrt(K))
     ldk = _ld(K, op_dtype)
@@ -1128,6 +1143,7 @@ def test_large_tiles_ragged_columns(op_dtype):
     # whole row blocks with a ragged last column tile (N = 1000 = 3 x 256 +
     # 232; 128 x 4 = 512 tiles, one work-group each), both output types
     B, K, N = 32768, 300, 1000
+    takes(True, routes.PROJECT, B, N, K, op_dtype)
     print("large tiles, ragged columns", _name(op_dtype), B, K, N, flush=True)
     X, Q = _mat(B, K, 87, op_dtype), _mat(N, K, 88, op_dtype, 1 / np.sqrt(K))
     ldk = _ld(K, op_dtype)
@@ -1167,15 +1183,16 @@ def test_large_tiles_unaligned_outputs(op_dtype, out_dtype):
     assert torch.isfinite(T.float()).all().item() and untouched(buf, N)
     assert rowrel(host(T[rows]), oracle.project(X[rows], Q)) <= tol
 
-    B, r, D = 8192, 45, 2100              # restore: 32 x 9 tiles
-    Tc, Qr = _mat(B, r, 94, op_dtype), _mat(r, D, 95, op_dtype)
-    buf, Xo = view(B, D)
-    gsm.gs_reconstruct(nan_padded(Tc, _ld(r, op_dtype), op_dtype), nan_padded(Qr, _ld(D, op_dtype, 8), op_dtype),
-                       out=Xo)
-    torch.cuda.synchronize()
-    rows = _tile_rows(B, 96)
-    assert torch.isfinite(Xo.float()).all().item() and untouched(buf, D)
-    assert rowrel(host(Xo[rows]), oracle.reconstruct(Tc[rows], Qr)) <= tol
+    for B, r, D in ((8192, 45, 2100), (16384, 45, 2100)):      # restore: 32 x 9 and 64 x 9 tiles
+        takes(B > 8192, routes.RESTORE, B, D, r, op_dtype, out_dtype)
+        Tc, Qr = _mat(B, r, 94, op_dtype), _mat(r, D, 95, op_dtype)
+        buf, Xo = view(B, D)
+        gsm.gs_reconstruct(nan_padded(Tc, _ld(r, op_dtype), op_dtype), nan_padded(Qr, _ld(D, op_dtype, 8), op_dtype),
+                           out=Xo)
+        torch.cuda.synchronize()
+        rows = _tile_rows(B, 96)
+        assert torch.isfinite(Xo.float()).all().item() and untouched(buf, D)
+        assert rowrel(host(Xo[rows]), oracle.reconstruct(Tc[rows], Qr)) <= tol
 
 
 # ------------- row sweep / scored products (>= 256 row blocks of 256, 256-column blocks)
@@ -1354,8 +1371,9 @@ def echelon_pair(M, r, dtype, seed):
 
 
 @pytest.mark.parametrize("op_dtype", OP_DTYPES, ids=_name)
-def test_echelon_prob2vec(op_dtype):
-    B, M, r = 8200, 2050, 2000
+@pytest.mark.parametrize("B,M,r", [(8200, 2050, 2000), (16300, 2050, 2030)])
+def test_echelon_prob2vec(op_dtype, B, M, r):
+    takes(B > 8200, routes.RESTORE, B, r, M, op_dtype, torch.float32)
     print("echelon prob2vec", _name(op_dtype), B, M, r, flush=True)
     P = wl.dirichlet_probs(B, M, 0.5, 41)
     if op_dtype == torch.bfloat16:

@@ -7,6 +7,7 @@ import pytest
 import torch
 
 from gpu_util import gamma
+from test_product_routes import BF16, F32, PROJECT, TILES128, route
 
 pytestmark = pytest.mark.gpu
 
@@ -201,3 +202,34 @@ def test_short_k(rows, K, cols, dtype, layout):
     buf, S = output(rows, cols, torch.float32, layout)
     gs.gs_similarity(X, Q, mode="dot", out=S, argmax=False)
     check(buf, S, x @ q.T, product_bound(x, q.T, K, torch.float32), cols)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+def test_strides_beyond_32_bit_offsets(dtype):
+    """Rows 2^22 elements apart (128 x 128 tiles: 64-bit addresses, here with
+    the long K ranges that the small tiles take otherwise)."""
+    gs = _gs()
+    rows, K, cols, ld = 37, 1001, 200, 1 << 22
+    ty = BF16 if dtype == torch.bfloat16 else F32
+    assert route(PROJECT, rows, cols, K, ty, ld=ld) == TILES128
+    g = torch.Generator(device="cuda")
+    g.manual_seed(25)
+    buf = torch.zeros(rows, ld, dtype=dtype, device="cuda")
+    X = buf[:, :K]
+    X.normal_(generator=g)
+    x = X.cpu().double().numpy()
+    Q, q = operand(cols, K, dtype, 26, "aligned")
+    B, b = operand(K, cols, dtype, 27, "aligned")
+    Y, y = operand(rows, K, dtype, 28, "aligned")
+    out, T = output(rows, cols, torch.float32, "aligned")
+    _, n2 = gs.gs_project(X, Q, out=T, xnorm2=True)
+    check(out, T, x @ q.T, product_bound(x, q.T, K, torch.float32), cols)
+    n64 = (x * x).sum(1)
+    assert np.all(np.abs(n2.cpu().double().numpy() - n64) <= gamma(K + 8) * n64)
+    out, Z = output(rows, cols, torch.float32, "aligned")
+    gs.gs_reconstruct(X, B, T2=Y, bind="mul", out=Z)
+    e1, e2 = product_bound(x, b, K, torch.float32), product_bound(y, b, K, torch.float32)
+    check(out, Z, (x @ b) * (y @ b), e1 * np.abs(y @ b) + e2 * np.abs(x @ b) + e1 * e2 + 1e-30, cols)
+    out, S = output(rows, cols, torch.float32, "aligned")
+    gs.gs_similarity(X, Q, mode="dot", out=S, argmax=False)
+    check(out, S, x @ q.T, product_bound(x, q.T, K, torch.float32), cols)
