@@ -110,7 +110,7 @@ WsLayout layout(int64_t M, int64_t D) {
     L.rank_after = o; o = align256(o + sizeof(int32_t) * M);
     L.kept = o;  o = align256(o + sizeof(int32_t) * M);
     L.flag = o;  o = align256(o + sizeof(int32_t));
-    L.pass2 = o; o = align256(o + sizeof(int32_t));
+    L.pass2 = o; o = align256(o + 2 * sizeof(int32_t));
     L.total = o;
     return L;
 }

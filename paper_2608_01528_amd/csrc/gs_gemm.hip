@@ -8,8 +8,9 @@
 //   bind         X = (T Q) .* (T2 Q)
 //   prob2vec     T = P R            (A = P,  B = R stored K x N)
 //   similarity   S = scale * T R^T  (A = T,  B = R stored N x K), cosine
-//                normalisation and row argmax fused in the epilogue
-//   attention    A = softmax(beta * S) fused, two passes over the row block
+//                normalisation fused in the epilogue (and the row argmax, where
+//                no score is written)
+//   attention    the scores times beta; a row pass makes them weights
 //
 // Work-group tile 128 x 128, K-step 32, 256 threads = 4 waves in a 2 x 2
 // arrangement, each wave owning a 64 x 64 sub-tile as 2 x 2 blocks of the
@@ -798,18 +799,15 @@ __global__ void __launch_bounds__(NTHR) gemm_scores_kernel(GemmArgs g, int veca,
         }
 }
 
-// ---------------------------------------- epilogue: similarity / softmax
+// ---------------------------------------- epilogue: argmax alone
 //
 // One work-group owns a 128-row block and sweeps every 128-column block of
 // the codebook.  Scores of a column block are parked in LDS, where one pair
-// of threads per row folds them into the row's running state: (max, argmax)
-// for similarity, (max, sum of exp) for softmax.  Softmax rows are finished
-// by a second sweep over the row block's outputs, which that same work-group
-// has just written (still in L2).
+// of threads per row folds them into the row's running (max, argmax).
 
 constexpr int SS_STRIDE = BN + 1;
 
-template <typename TA, typename TB, bool SOFTMAX>
+template <typename TA, typename TB>
 __global__ void __launch_bounds__(NTHR) gemm_rowsweep_kernel(GemmArgs g, int veca, int vecb) {
     extern __shared__ float lds[];
     float *ss = lds + stage_lds_floats<TA, TB, false, SWEEP_STAGES>(g.dma);   // scores [BM][SS_STRIDE]
@@ -823,12 +821,10 @@ __global__ void __launch_bounds__(NTHR) gemm_rowsweep_kernel(GemmArgs g, int vec
     const int t = threadIdx.x;
     const int l = t & 63, w = t >> 6;
     const int wm = (w >> 1) * 64, wn = (w & 1) * 64;
-    float *out = static_cast<float *>(g.C);
-    const bool vec_out = (reinterpret_cast<uintptr_t>(out) & 15) == 0 && g.ldc % 4 == 0;
 
     // running row state, identical in both threads of a pair
     const int prow = t >> 1, half = t & 1;
-    float run_max = -INFINITY, run_sum = 0.f;
+    float run_max = -INFINITY;
     int run_idx = 0;
 
     for (int64_t nt = 0; nt < nN; ++nt) {
@@ -855,8 +851,7 @@ __global__ void __launch_bounds__(NTHR) gemm_rowsweep_kernel(GemmArgs g, int vec
             cn[t] = c;
         }
         lds_barrier();
-        // scores -> LDS and (optionally) global
-        const float mul = SOFTMAX ? g.scale * g.beta : g.scale;
+        // scores -> LDS
 #pragma unroll
         for (int i = 0; i < 2; ++i)
 #pragma unroll
@@ -866,72 +861,28 @@ __global__ void __launch_bounds__(NTHR) gemm_rowsweep_kernel(GemmArgs g, int vec
 #pragma unroll
                 for (int r = 0; r < 16; ++r) {
                     const int rl = wm + 32 * i + acc_row(r, l);
-                    const float v = mul * acc[i][j][r] * rq[rl] * cn[cl];
+                    const float v = g.scale * acc[i][j][r] * rq[rl] * cn[cl];
                     ss[rl * SS_STRIDE + cl] = (col < g.N) ? v : -INFINITY;
                 }
             }
         lds_barrier();
-        if (SOFTMAX || g.write_out) {
-            // the block's scores leave from the LDS tile, four columns per
-            // thread: rows t / 32 + 8 q, columns 4 (t % 32) .. + 3
-            const int c4 = 4 * (t & 31);
-            const int64_t col = n0 + c4;
-            for (int q = 0; q < 16; ++q) {
-                const int rl = (t >> 5) + 8 * q;
-                const int64_t row = m0 + rl;
-                if (row >= g.M || col >= g.N) continue;
-                const float *src = ss + rl * SS_STRIDE + c4;
-                float *dst = out + row * g.ldc + col;
-                if (vec_out && col + 4 <= g.N) {
-                    *reinterpret_cast<f4v *>(dst) = f4v{src[0], src[1], src[2], src[3]};
-                } else {
-                    for (int e = 0; e < 4 && col + e < g.N; ++e) dst[e] = src[e];
-                }
-            }
-        }
         // fold this column block into the running row state
         const int ncols = (int)((g.N - n0 < BN) ? (g.N - n0) : BN);
-        float bm = -INFINITY, bs = 0.f;
+        float bm = -INFINITY;
         int bi = 0;
         for (int c = half; c < ncols; c += 2) {
             float v = ss[prow * SS_STRIDE + c];
             if (v > bm) { bm = v; bi = c; }
         }
-        if (SOFTMAX) {
-            for (int c = half; c < ncols; c += 2) bs += __expf(ss[prow * SS_STRIDE + c] - bm);
-        }
-        float om = __shfl_xor(bm, 1), os = __shfl_xor(bs, 1);
-        int oi = __shfl_xor(bi, 1);
-        if (SOFTMAX) {
-            float nm = fmaxf(bm, om);
-            float tsum = (bm == -INFINITY ? 0.f : bs * __expf(bm - nm)) +
-                         (om == -INFINITY ? 0.f : os * __expf(om - nm));
-            float m2 = fmaxf(run_max, nm);
-            run_sum = (run_max == -INFINITY ? 0.f : run_sum * __expf(run_max - m2)) +
-                      (nm == -INFINITY ? 0.f : tsum * __expf(nm - m2));
-            run_max = m2;
-        } else {
-            // lowest column index wins a tie
-            if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
-            if (bm > run_max) { run_max = bm; run_idx = (int)(n0 + bi); }
-        }
+        const float om = __shfl_xor(bm, 1);
+        const int oi = __shfl_xor(bi, 1);
+        // lowest column index wins a tie
+        if (om > bm || (om == bm && oi < bi)) { bm = om; bi = oi; }
+        if (bm > run_max) { run_max = bm; run_idx = (int)(n0 + bi); }
         lds_barrier();   // ss and the staged tiles are reused by the next block
     }
 
-    if (!SOFTMAX) {
-        if (g.argmax && half == 0 && m0 + prow < g.M) g.argmax[m0 + prow] = run_idx;
-        return;
-    }
-    // second sweep: normalise the row block
-    float *rmax = rq, *rinv = cn;   // reuse
-    if (half == 0) {
-        rmax[prow] = run_max;
-        rinv[prow] = 1.f / run_sum;
-    }
-    // the second sweep reads scores that other threads stored to global
-    // memory: a full barrier (their stores complete and visible)
-    __syncthreads();
-    softmax_rows(out, g.ldc, m0, (g.M - m0 < BM) ? (g.M - m0) : BM, g.N, rmax, rinv, vec_out, NTHR);
+    if (g.argmax && half == 0 && m0 + prow < g.M) g.argmax[m0 + prow] = run_idx;
 }
 
 template <typename K>
@@ -974,12 +925,11 @@ hipError_t dispatch_scores(bool softmax, const GemmArgs &a_in, bool veca, bool v
 }
 
 template <typename TA, typename TB>
-hipError_t dispatch_rowsweep(bool softmax, const GemmArgs &a, bool veca, bool vecb, hipStream_t s) {
+hipError_t dispatch_rowsweep(const GemmArgs &a, bool veca, bool vecb, hipStream_t s) {
     const int64_t nM = (a.M + BM - 1) / BM;
     const dim3 grid((unsigned)(8 * ((nM + 7) / 8)));
     const size_t lds = (stage_lds_floats<TA, TB, false, SWEEP_STAGES>(a.dma) + BM * SS_STRIDE + 2 * BM) * sizeof(float);
-    if (softmax) return launch_with_lds(gemm_rowsweep_kernel<TA, TB, true>, grid, lds, s, a, veca, vecb);
-    return launch_with_lds(gemm_rowsweep_kernel<TA, TB, false>, grid, lds, s, a, veca, vecb);
+    return launch_with_lds(gemm_rowsweep_kernel<TA, TB>, grid, lds, s, a, veca, vecb);
 }
 
 bool aligned16(const void *p) { return (reinterpret_cast<uintptr_t>(p) & 15u) == 0; }
@@ -1085,7 +1035,7 @@ hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi e
     const Route route = product_route(ta, tb, tout, b_nn, epi, a);
     if (route == ROUTE_FEW_ROWS) return launch_few_rows(ta, a, sm, s);
     if (route == ROUTE_SPLIT) return launch_split(ta, tout, b_nn, epi, a, s);
-    if (route == ROUTE_SWEEP256) return launch_sweep256(ta, sm, a, s);
+    if (route == ROUTE_SWEEP256) return launch_sweep256(ta, a, s);
     if (route == ROUTE_TILES256 && (epi == EPI_SIM || sm)) return launch_scores256(ta, a, sm, s);
     if (route == ROUTE_TILES256 && epi == EPI_STORE) return launch_gemm256(ta, tout, b_nn, a, s);
     if (route == ROUTE_TILES256) {
@@ -1121,8 +1071,8 @@ hipError_t launch_gemm(gs_dtype ta, gs_dtype tb, gs_dtype tout, bool b_nn, Epi e
         if (!bf_a && !bf_b) return dispatch_scores<float, float>(sm, a, veca, vecb, s);
         if (bf_a && bf_b) return dispatch_scores<bf16_t, bf16_t>(sm, a, veca, vecb, s);
     }
-    if (!bf_a && !bf_b) return dispatch_rowsweep<float, float>(sm, a, veca, vecb, s);
-    if (bf_a && bf_b) return dispatch_rowsweep<bf16_t, bf16_t>(sm, a, veca, vecb, s);
+    if (!bf_a && !bf_b) return dispatch_rowsweep<float, float>(a, veca, vecb, s);
+    if (bf_a && bf_b) return dispatch_rowsweep<bf16_t, bf16_t>(a, veca, vecb, s);
     return hipErrorInvalidValue;
 }
 

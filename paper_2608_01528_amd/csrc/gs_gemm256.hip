@@ -471,10 +471,14 @@ __device__ __forceinline__ void mma_256(const GemmArgs &g, const TileLoads<T, BN
 // row) collide on banks.
 //
 // Both operands are scaled by 2^16 on the way (and the sums by 2^-32), so that
-// the low parts of any normal fp32 value are normal numbers too.  What has no
-// such parts (infinities, NaN, values of 2^111 and up, sums past the range)
-// leaves a sum that is not finite: the caller then runs the tile once more
-// with fp32 MFMAs.
+// the parts of every normal fp32 value can be held: normal numbers from 2^-119
+// up; below, the last plane may be subnormal, which the subtractions keep and
+// the bf16 MFMAs take as it is.  What has no such parts (infinities, NaN,
+// values of 2^111 and up, sums past 2^96) leaves a sum that is not finite: the
+// caller then runs the tile once more with fp32 MFMAs, and it takes both times
+// (project 65536 x 8192 x 256 with one such row in every tile 3.6 ms, without
+// 1.49, fp32 MFMAs alone 1.89).  A look at the sums after 512 k, which would
+// spare most of the first run, costs every call 0.6 %.
 //
 // What bounds it is power: the matrix cores are busy 59 % of the time at 1.83
 // GHz (bf16 operands: 73 % at 1.42).  65536 x 256 x 8192 (project): 1.94 ms with
@@ -1114,39 +1118,26 @@ scores256_kernel(GemmArgs g) {
     }
 }
 
-// ------------------------------------------------ similarity / softmax sweep
+// ------------------------------------------------ argmax sweep
 //
 // One work-group owns 256 query rows and sweeps the codebook in column blocks
 // of 256 with the same product loop (B = R stored N x K).  After each block,
-// the scaled scores of one half of the rows at a time (rows wm + 64 h ..
-// + 63 of each wave) are staged in LDS: from there they are stored (scores
-// requested, or raw softmax scores for the second pass) with 16-byte row
-// chunks, and two threads per row fold them into the row's running state:
-// (max, lowest index of the max) for similarity, (max, sum of exp) for
-// softmax.  Softmax rows are finished by a second pass over the row block's
-// stored scores.
+// the accumulators of one half of the rows at a time (rows wm + 64 h ..
+// + 63 of each wave) are staged in LDS, where two threads per row scale them
+// and fold them into the row's running (max, lowest index of the max).  No
+// score leaves the chip.
 
-// (max, sum of exp(x - max)) pairs
-__device__ __forceinline__ void fold_sum(float &m, float &z, float m2, float z2) {
-    const float mx = fmaxf(m, m2);
-    const float a = (m == -INFINITY) ? 0.f : z * __expf(m - mx);
-    const float b = (m2 == -INFINITY) ? 0.f : z2 * __expf(m2 - mx);
-    m = mx;
-    z = a + b;
-}
-
-constexpr size_t SWEEP_LDS_BYTES = LDS_BYTES + 4 * TM * sizeof(float);   // + rq, cn, rmax, rinv
+constexpr size_t SWEEP_LDS_BYTES = LDS_BYTES + 2 * TM * sizeof(float);   // + rq, cn
 
 // ROWN: row norms of T from its fragments (cosine without qnorm2); COLN:
 // column norms of R from its fragments (cosine without cnorm).
-template <typename T, bool SOFTMAX, bool ROWN, bool COLN>
+template <typename T, bool ROWN, bool COLN>
 __global__ void __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(1, 1)))
 sweep256_kernel(GemmArgs g) {
     extern __shared__ float lds_f[];
     uint16_t *lds = reinterpret_cast<uint16_t *>(lds_f);
     float *rq = lds_f + LDS_BYTES / sizeof(float);   // 1 / ||x|| per row (or 1)
     float *cn = rq + TM;                             // 1 / ||c|| per column of the block (or 1)
-    float *rmax = cn + TN, *rinv = rmax + TM;        // softmax row results
     const int64_t nM = (g.M + TM - 1) / TM, nN = (g.N + TN - 1) / TN;
     // row blocks dealt to the XCDs in contiguous ranges: the blocks one XCD
     // runs together sweep the same codebook block at about the same time
@@ -1156,16 +1147,11 @@ sweep256_kernel(GemmArgs g) {
     const int64_t m0 = lt * TM;
     const int t = threadIdx.x, l = t & 63, w = t >> 6;
     const int wm = (w >> 1) * 128, wn = (w & 1) * 128;
-    float *out = static_cast<float *>(g.C);
-    const bool write = SOFTMAX || g.write_out;
-    const bool interior_rows = m0 + TM <= g.M;
-    const bool vec_out = (reinterpret_cast<uintptr_t>(out) & 15) == 0 && g.ldc % 4 == 0;
-    const float mul = SOFTMAX ? g.scale * g.beta : g.scale;
     // the staged half h holds rows wm + 64 h + (0 .. 63) of every wave; thread
     // pair (t, t ^ 1) folds staged row t / 2 of that half: wave region
     // 2 (t / 128) + (t & 1), local row (t / 2) % 64
     const int srow = (t >> 1) & 63, sreg = 2 * (t >> 7) + (t & 1);
-    float run_m[2] = {-INFINITY, -INFINITY}, run_z[2] = {0.f, 0.f};
+    float run_m[2] = {-INFINITY, -INFINITY};
     int run_i[2] = {0, 0};
 
     constexpr int STRIDE = 128 * 4 + 32;             // staged fp32 row: 128 values + pad
@@ -1233,33 +1219,13 @@ sweep256_kernel(GemmArgs g) {
                         *reinterpret_cast<float *>(region + row * STRIDE + col * 4) = acc[2 * h + ii][j][r];
                     }
             lds_barrier();
-            // score of staged (row, 4 columns): raw * (mul / (||x|| ||c||)), one
-            // expression for the stored scores and the fold
-            if (write) {
-                const bool full = vec_out && interior_rows && n0 + wn + 128 <= g.N;
-#pragma unroll 4
-                for (int id = l; id < 64 * 32; id += 64) {
-                    const int rr = id >> 5, cc = id & 31;
-                    const int64_t grow = m0 + wm + 64 * h + rr, gcol = n0 + wn + 4 * cc;
-                    const f4v raw = *reinterpret_cast<const f4v *>(region + rr * STRIDE + cc * 16);
-                    const f4v cf = *reinterpret_cast<const f4v *>(cn + wn + 4 * cc);
-                    const f4v v = raw * (mul * rq[wm + 64 * h + rr]) * cf;
-                    float *dst = out + grow * g.ldc + gcol;
-                    if (full) {
-                        *reinterpret_cast<f4v *>(dst) = v;
-                    } else if (grow < g.M) {
-                        for (int e = 0; e < 4; ++e)
-                            if (gcol + e < g.N) dst[e] = v[e];
-                    }
-                }
-            }
             // fold: thread t scans the 128 staged columns of its row, then pairs up
             {
                 const float *src = reinterpret_cast<const float *>(
                     reinterpret_cast<const unsigned char *>(lds) + sreg * (64 * STRIDE) + srow * STRIDE);
                 const int half = 128 * (t & 1);
-                const float f = mul * rq[128 * (t >> 7) + 64 * h + srow];
-                float m = -INFINITY, z = 0.f;
+                const float f = g.scale * rq[128 * (t >> 7) + 64 * h + srow];
+                float m = -INFINITY;
                 int mi = 0;
 #pragma unroll 2
                 for (int c4 = 0; c4 < 32; ++c4) {
@@ -1271,26 +1237,11 @@ sweep256_kernel(GemmArgs g) {
                         if (c < ncols && v[e] > m) { m = v[e]; mi = (int)n0 + c; }
                     }
                 }
-                if (SOFTMAX && m != -INFINITY) {
-#pragma unroll 2
-                    for (int c4 = 0; c4 < 32; ++c4) {
-                        const f4v v = *reinterpret_cast<const f4v *>(src + 4 * c4) * f *
-                                      *reinterpret_cast<const f4v *>(cn + half + 4 * c4);
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (half + 4 * c4 + e < ncols) z += __expf(v[e] - m);
-                    }
-                }
                 // the partner thread holds the other 128 columns of the row
-                const float m2 = __shfl_xor(m, 1), z2 = __shfl_xor(z, 1);
+                const float m2 = __shfl_xor(m, 1);
                 const int i2 = __shfl_xor(mi, 1);
-                if (SOFTMAX) {
-                    fold_sum(m, z, m2, z2);
-                    fold_sum(run_m[h], run_z[h], m, z);
-                } else {
-                    fold_max(m, mi, m2, i2);
-                    fold_max(run_m[h], run_i[h], m, mi);
-                }
+                fold_max(m, mi, m2, i2);
+                fold_max(run_m[h], run_i[h], m, mi);
             }
             lds_barrier();    // the staging region is rewritten next
         }
@@ -1298,34 +1249,20 @@ sweep256_kernel(GemmArgs g) {
 
     // rows owned by thread pair (t, t ^ 1) in half h: wm + 64 h + srow of wave
     // region sreg, i.e. 128 (t / 128) + 64 h + srow
-    if (!SOFTMAX) {
-        if (g.argmax && (t & 1) == 0) {
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                const int64_t row = m0 + 128 * (t >> 7) + 64 * h + srow;
-                if (row < g.M) g.argmax[row] = run_i[h];
-            }
-        }
-        return;
-    }
-    if ((t & 1) == 0) {
+    if (g.argmax && (t & 1) == 0) {
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
-            const int rl = 128 * (t >> 7) + 64 * h + srow;
-            rmax[rl] = run_m[h];
-            rinv[rl] = 1.f / run_z[h];
+            const int64_t row = m0 + 128 * (t >> 7) + 64 * h + srow;
+            if (row < g.M) g.argmax[row] = run_i[h];
         }
     }
-    // the second pass reads scores other threads stored to global memory
-    __syncthreads();
-    softmax_rows(out, g.ldc, m0, (g.M - m0 < TM) ? (g.M - m0) : TM, g.N, rmax, rinv, vec_out, NTH);
 }
 
 template <typename T, typename TO>
 hipError_t launch_to(bool b_nn, const GemmArgs &a, hipStream_t s) {
     // Tiles of equal work (all interior, the whole K range): one persistent
-    // work-group per CU (256 CUs, 32 per XCD; the tile count is at least 256,
-    // gemm256_fits).  Otherwise one work-group per tile, so the dispatcher
+    // work-group per CU (256 CUs, 32 per XCD; with fewer tiles the rest end at
+    // once).  Otherwise one work-group per tile, so the dispatcher
     // balances tiles of unequal work (edge tiles, echelon K ranges), which a
     // fixed stride would let drift apart and lose their shared L2 slices.
     const int64_t total = ((a.M + TM - 1) / TM) * ((a.N + TN - 1) / TN);
@@ -1615,22 +1552,22 @@ __global__ void __launch_bounds__(256) few_rows_kernel(GemmArgs g) {
     }
 }
 
-template <typename T, bool SOFTMAX, bool ROWN, bool COLN>
+template <typename T, bool ROWN, bool COLN>
 hipError_t launch_sweep(const GemmArgs &a, hipStream_t s) {
     const int64_t nM = (a.M + TM - 1) / TM;
     const dim3 grid((unsigned)(8 * ((nM + 7) / 8)));
-    const void *k = reinterpret_cast<const void *>(sweep256_kernel<T, SOFTMAX, ROWN, COLN>);
+    const void *k = reinterpret_cast<const void *>(sweep256_kernel<T, ROWN, COLN>);
     hipError_t e = raise_lds_limit(k, SWEEP_LDS_BYTES);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((sweep256_kernel<T, SOFTMAX, ROWN, COLN>), grid, dim3(NTH), SWEEP_LDS_BYTES, s, a);
+    hipLaunchKernelGGL((sweep256_kernel<T, ROWN, COLN>), grid, dim3(NTH), SWEEP_LDS_BYTES, s, a);
     return hipGetLastError();
 }
 
-template <typename T, bool SOFTMAX>
+template <typename T>
 hipError_t launch_sweep_norms(const GemmArgs &a, hipStream_t s) {
     const bool rown = a.cosine && a.qnorm2 == nullptr, coln = a.cosine && a.cnorm == nullptr;
-    if (rown) return coln ? launch_sweep<T, SOFTMAX, true, true>(a, s) : launch_sweep<T, SOFTMAX, true, false>(a, s);
-    return coln ? launch_sweep<T, SOFTMAX, false, true>(a, s) : launch_sweep<T, SOFTMAX, false, false>(a, s);
+    if (rown) return coln ? launch_sweep<T, true, true>(a, s) : launch_sweep<T, true, false>(a, s);
+    return coln ? launch_sweep<T, false, true>(a, s) : launch_sweep<T, false, false>(a, s);
 }
 
 template <typename T, int FUSE>
@@ -1733,10 +1670,9 @@ bool sweep256_fits(gs_dtype t, const GemmArgs &a) {
     return es * (TM * a.lda + a.K + 8) < lim && es * (TN * a.ldb + a.K + 8) < lim;
 }
 
-hipError_t launch_sweep256(gs_dtype t, bool softmax, const GemmArgs &a, hipStream_t s) {
+hipError_t launch_sweep256(gs_dtype t, const GemmArgs &a, hipStream_t s) {
     if (a.M == 0 || a.N == 0) return hipSuccess;
-    if (t == GS_BF16) return softmax ? launch_sweep_norms<bf16_t, true>(a, s) : launch_sweep_norms<bf16_t, false>(a, s);
-    return softmax ? launch_sweep_norms<float, true>(a, s) : launch_sweep_norms<float, false>(a, s);
+    return t == GS_BF16 ? launch_sweep_norms<bf16_t>(a, s) : launch_sweep_norms<float>(a, s);
 }
 
 bool gemm256_fits(gs_dtype t, const GemmArgs &a, bool b_nn) {
